@@ -632,7 +632,9 @@ rl_status run_gemm_plan(rl_decode_ctx* c, int kc, const GemmPlan* plan, const vo
         return RL_OK;
     }
     GemmArgs g = a;
-    if (epi != EPI_F32) { g.out_f32 = a.partial; g.ldo = Nw; }
+    // K is a multiple of 8 in every configuration, so few rows always take that kernel
+    const bool fused = epi == EPI_F32 || (epi == EPI_SWIGLU && gemm_f32_few_rows(M, n_out));
+    if (!fused) { g.out_f32 = a.partial; g.ldo = Nw; g.epi = EPI_F32; }
     {
         Prof pr(c, kc);
         e = launch_gemm_f32(g, c->stream);
@@ -643,7 +645,7 @@ rl_status run_gemm_plan(rl_decode_ctx* c, int kc, const GemmPlan* plan, const vo
         *splits = 1;
         return RL_OK;
     }
-    if (epi != EPI_F32) {
+    if (!fused) {
         Prof pr(c, RL_K_SPLITK_REDUCE);
         e = launch_splitk_reduce(DT_F32, a, 1, a.partial, c->stream);
         if (e != hipSuccess) return hip_fail(c, e, "epilogue launch");

@@ -881,8 +881,102 @@ hipError_t launch_mfma_probe(int n_blocks, int iters, float* out, hipStream_t s)
 }
 
 // ---------------------------------------------------------------------------
-// fp32 VALU kernel: out_f32[m][n] = sum_k A[m][k] W[n][k]
-// 32 x 64 output tile, 2 x 4 per thread, k tiles of 32 through LDS.
+// fp32 VALU kernels: out[m][n] = sum_k A[m][k] W[n][k].
+//
+// Few rows: one workgroup owns 16 weight rows (SwiGLU: 16 gate rows and the
+// matching up rows) and MR activation rows; 16 lanes share a weight row,
+// each with every 16th float4 of it, and their sums meet in a lane tree.
+// What bounds these shapes is latency: the tiled kernel below walks its k
+// tiles one memory round trip and two barriers after the other, here every
+// load of 256 k is in flight at once (8 rows, N 256, K 688: 70.8 -> 6.2 us; 64
+// rows, N 1376, K 256: 29.6 -> 6.1).
+// ---------------------------------------------------------------------------
+template <int MR, int EPI>
+__global__ void __launch_bounds__(256) gemm_f32_rows_kernel(GemmArgs p) {
+    constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;   // weight rows per lane group (gate, up)
+    constexpr int U = 4;                            // float4 of each row per batch of loads
+    const int ks = threadIdx.x & 15;
+    const int n = blockIdx.x * 16 + (threadIdx.x >> 4);
+    const int n_out = EPI == EPI_SWIGLU ? p.F : p.Nw;
+    const int m0 = blockIdx.y * MR;
+    const bool ok = n < n_out;
+    const float* wp[NW];
+#pragma unroll
+    for (int j = 0; j < NW; ++j)
+        wp[j] = static_cast<const float*>(p.W) + (static_cast<size_t>(ok ? n : 0) + static_cast<size_t>(j) * p.F) * p.ldw;
+    const float* ap[MR];
+#pragma unroll
+    for (int i = 0; i < MR; ++i)   // rows past M repeat the last one and are not stored
+        ap[i] = static_cast<const float*>(p.A) + static_cast<size_t>(min(m0 + i, p.M - 1)) * p.lda;
+    float acc[NW][MR];
+#pragma unroll
+    for (int j = 0; j < NW; ++j)
+#pragma unroll
+        for (int i = 0; i < MR; ++i) acc[j][i] = 0.0f;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 4 * ks; k0 < p.K; k0 += 64 * U) {
+        f32x4 w[U][NW], a[U][MR];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + 64 * u;
+            const bool in = k < p.K;   // K is a multiple of 4
+#pragma unroll
+            for (int j = 0; j < NW; ++j) w[u][j] = in ? *reinterpret_cast<const f32x4*>(wp[j] + k) : zero;
+#pragma unroll
+            for (int i = 0; i < MR; ++i) a[u][i] = in ? *reinterpret_cast<const f32x4*>(ap[i] + k) : zero;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < NW; ++j)
+#pragma unroll
+                for (int i = 0; i < MR; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[j][i] = fmaf(w[u][j][e], a[u][i][e], acc[j][i]);
+    }
+#pragma unroll
+    for (int j = 0; j < NW; ++j)
+#pragma unroll
+        for (int i = 0; i < MR; ++i)
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) acc[j][i] += __shfl_xor(acc[j][i], o, 64);
+#pragma unroll
+    for (int i = 0; i < MR; ++i) {
+        const int m = m0 + i;
+        if (ks != i || !ok || m >= p.M) continue;
+        if (EPI == EPI_SWIGLU)
+            static_cast<float*>(p.act)[static_cast<size_t>(m) * p.ld_act + n] = swiglu_f32(acc[0][i], acc[NW - 1][i]);
+        else
+            p.out_f32[static_cast<size_t>(m) * p.ldo + n] = acc[0][i];
+    }
+}
+
+// Up to 6144 workgroups of the few-rows kernel it is the faster one (512 rows x
+// 1376, K 256, 5504 workgroups: 28 us against 34); beyond, its repeated
+// activation loads cost more than the tiled kernel's chain (512 x 4096, 16384
+// workgroups: 77 us against 47).
+bool gemm_f32_few_rows(int M, int n_out) {
+    return static_cast<long>(ceil_div(M, M <= 2 ? 2 : M <= 4 ? 4 : 8)) * ceil_div(n_out, 16) <= 6144;
+}
+
+static hipError_t launch_gemm_f32_rows(const GemmArgs& a, hipStream_t s) {
+    const int n_out = a.epi == EPI_SWIGLU ? a.F : a.Nw;
+#define RL_FR(MR)                                                                                           \
+    do {                                                                                                    \
+        const dim3 grid(ceil_div(n_out, 16), ceil_div(a.M, MR));                                            \
+        if (a.epi == EPI_SWIGLU) hipLaunchKernelGGL((gemm_f32_rows_kernel<MR, EPI_SWIGLU>), grid, dim3(256), 0, s, a); \
+        else hipLaunchKernelGGL((gemm_f32_rows_kernel<MR, EPI_F32>), grid, dim3(256), 0, s, a);              \
+    } while (0)
+    if (a.M <= 2) RL_FR(2);
+    else if (a.M <= 4) RL_FR(4);
+    else RL_FR(8);
+#undef RL_FR
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// fp32, more rows: 32 x 64 output tile, 2 x 4 per thread, k tiles of 32 through
+// LDS.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__ A, int lda,
         const float* __restrict__ W, int ldw, int M, int N, int K, float* __restrict__ out, int ldo) {
@@ -930,6 +1024,8 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__
 
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
     if (a.M <= 0) return hipSuccess;
+    if (a.K % 4 == 0 && gemm_f32_few_rows(a.M, a.epi == EPI_SWIGLU ? a.F : a.Nw)) return launch_gemm_f32_rows(a, s);
+    if (a.epi != EPI_F32) return hipErrorInvalidValue;
     dim3 grid(ceil_div(a.Nw, 64), ceil_div(a.M, 32));
     hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, s, static_cast<const float*>(a.A), a.lda,
                        static_cast<const float*>(a.W), a.ldw, a.M, a.Nw, a.K, a.out_f32, a.ldo);

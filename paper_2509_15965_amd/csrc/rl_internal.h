@@ -163,7 +163,9 @@ hipError_t launch_resid_norm(int dt, const float* part, int splits, float* x, in
 
 hipError_t launch_gemm_bf16(const GemmArgs& a, const GemmPlan& p, hipStream_t s);
 hipError_t launch_gemm_bf16_lds(const GemmArgs& a, const GemmPlan& p, hipStream_t s);
-hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s);   // writes a.out_f32 [M][Nw]
+// writes a.out_f32 [M][Nw]; with EPI_SWIGLU (only where gemm_f32_few_rows holds) a.act
+hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s);
+bool gemm_f32_few_rows(int M, int n_out);   // the kernel for few rows serves this fp32 GEMM
 hipError_t launch_splitk_reduce(int dt, const GemmArgs& a, int splits, const float* partial,
                                 hipStream_t s);
 
