@@ -39,9 +39,6 @@ constexpr TileKernel kLineTiles[] = {   // ties go to the earlier entry (weights
     {kLineVariant128x256, 128, 256, 1, 19.5, 19.5},
     {kLineVariant128x128Deep, 128, 128, 1, 12.0, 12.0},
 };
-constexpr int kCUs = 256;
-
-struct Cost { double us; };
 
 double rounds_us(const TileKernel& t, long tiles, double kfrac) {
     const long per_cu = (tiles + kCUs - 1) / kCUs;
@@ -55,6 +52,24 @@ long tiles_of(const TileKernel& t, int M, int n_cols, int epi) {
 }
 
 }  // namespace
+
+// A tile grid of 256 x 256 tiles past its whole rounds leaves `rem` tiles for a
+// last round that would keep 256 - rem CUs idle; cut in K, up to 256 / rem
+// slices each, they fill it for 1 / splits of the time.  A slice keeps at
+// least 256 of K (four pipeline stages), and all partial tiles together (at
+// most 256) fit the split-K partials.
+RemainderCut remainder_cut(int tiles, int K) {
+    RemainderCut c{0, 1, K};
+    const int rem = tiles % kCUs;
+    if (tiles < kCUs || rem == 0 || K % 64 != 0) return c;
+    int s = kCUs / rem;
+    s = s > K / 256 ? K / 256 : s > 16 ? 16 : s;
+    if (s < 2) return c;
+    c.tiles = rem;
+    c.ks = ceil_div(ceil_div(K, s), 64) * 64;
+    c.splits = ceil_div(K, c.ks);
+    return c;
+}
 
 // Direct-load kernel plan for M <= 64 (its own split-K heuristic: split until
 // about 1024 workgroups stream the weight).
@@ -157,9 +172,22 @@ GemmPlan plan_gemm_bf16(int M, int Nw, int K, int epi, int F) {
             }
         }
     }
-    // whole rounds of 256 x 256 tiles, then the rest of the columns
     const TileKernel& big = kLineTiles[0];
     const long big_tiles = tiles_of(big, M, n_out, epi);
+    // whole rounds of 256 x 256 tiles, the remainder cut in K; its partial
+    // tiles are written and read back once (8 bytes an element and slice)
+    const RemainderCut cut = big_tiles < (1L << 30) ? remainder_cut(static_cast<int>(big_tiles), K) : RemainderCut{0, 1, K};
+    if (cut.splits > 1) {
+        double us = (big_tiles / kCUs) * big.t_round * (K / 1024.0) + big.t_round * (cut.ks / 1024.0) +
+                    8.0 * 65536 * cut.tiles * cut.splits / 4.0e6 + 4.0;
+        us = (us > floor_us ? us : floor_us) + out_us + fixed;
+        if (us < best * 0.98) {
+            best = us;
+            best_p = GemmPlan{};
+            best_p.variant = kLineVariant256x256Cut; best_p.splits = 1; best_p.ksplit = K;
+        }
+    }
+    // whole rounds of 256 x 256 tiles, then the rest of the columns
     const int m_tiles = ceil_div(M, big.BM);
     const int bno = epi == EPI_SWIGLU ? big.BN / 2 : big.BN;
     const long full_cols = (big_tiles / kCUs) * kCUs / m_tiles;   // n tiles of whole rounds
@@ -244,6 +272,11 @@ int plan_gemm_candidates(int M, int Nw, int K, int epi, int F, GemmPlan* out, in
     }
     const TileKernel& big = kLineTiles[0];
     const long big_tiles = tiles_of(big, M, n_out, epi);
+    if (big_tiles < (1L << 30) && remainder_cut(static_cast<int>(big_tiles), K).splits > 1) {
+        GemmPlan p{};
+        p.variant = kLineVariant256x256Cut; p.splits = 1; p.ksplit = K;
+        add(p);
+    }
     const int m_tiles = ceil_div(M, big.BM);
     const int bno = epi == EPI_SWIGLU ? big.BN / 2 : big.BN;
     const long full_cols = (big_tiles / kCUs) * kCUs / m_tiles;
@@ -263,6 +296,7 @@ int64_t gemm_plan_code_of(const GemmPlan& p) {
     auto code = [](int v) -> int64_t {
         switch (v) {
             case kLineVariant256x256: return RL_GEMM_T256;
+            case kLineVariant256x256Cut: return RL_GEMM_T256;   // the same tiles, the last of them cut in K
             case kLineVariant128x256: return RL_GEMM_T128X256;
             case kLineVariant128x128: return RL_GEMM_T128;
             case kLineVariant128x128Deep: return RL_GEMM_T128_DEEP;

@@ -432,9 +432,23 @@ __device__ __forceinline__ void wait_vm_atmost(int n) {
     else wait_vm<0>();
 }
 
-template <int BM, int BN, int WM, int NW, int SA, int SW, int EPI, bool SPLIT>
-__global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ksplit, int m_tiles, int n_tiles, int n0,
-                                                              int gm, int xsplit) {
+// Which tile and K slice a workgroup of gemm_dma128_kernel computes.  Tiles
+// are numbered m-fastest inside groups of gm row tiles; workgroup 8j + x runs
+// on XCD x and takes the j-th tile of that XCD's eighth of the numbering, so
+// every XCD has the same number of tiles (within one) and the tiles it runs
+// together share their row or column operands in its L2.
+struct TileMap {
+    int m_tiles, n_tiles, gm;
+    int whole;    // tiles [0, whole) run over their K slice (blockIdx.y), one workgroup each
+    int rem;      // tiles [whole, whole + rem) are cut into rem_splits K slices of rem_ks,
+    int rem_splits, rem_ks;   // whose fp32 tiles go to the partials buffer (launch_dma128)
+    int xsplit;   // split-K over the XCDs (see the kernel)
+};
+
+// MODE 0: whole tiles with the epilogue; 1: split-K, partial tiles [split][M][Nw];
+// 2: whole tiles with the epilogue and a K-cut remainder (TileMap::rem)
+template <int BM, int BN, int WM, int NW, int SA, int SW, int EPI, int MODE>
+__global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ksplit, TileMap tm, int n0) {
     constexpr int BK = 64, ROWB = 128;
     constexpr int WN = NW / WM;
     constexpr int TM = BM / WM, TN = BN / WN;
@@ -451,22 +465,34 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
     const int w = blockIdx.x;
     const int xcd = w & 7, j = w >> 3;
     int m_tile, n_tile, split;
-    if (xsplit) {
+    int cut = -1;   // MODE 2: partial tile written by a remainder workgroup
+    if (tm.xsplit) {
         // split-K over the XCDs: XCD x % 8 runs split 8y + x % 8 of every tile
         // (M tiles fastest), so its K range of the activations stays in its L2
         // and the M tiles of one weight tile run back to back
         split = static_cast<int>(blockIdx.y) * 8 + xcd;
-        m_tile = j % m_tiles;
-        n_tile = j / m_tiles;
-        if (split * ksplit >= p.K || n_tile >= n_tiles) return;
+        m_tile = j % tm.m_tiles;
+        n_tile = j / tm.m_tiles;
+        if (split * ksplit >= p.K || n_tile >= tm.n_tiles) return;
     } else {
-        const int ntx = (n_tiles + 7) >> 3;
-        const int grp = j / (gm * ntx);
-        const int rem = j - grp * gm * ntx;
-        m_tile = grp * gm + rem % gm;
-        n_tile = (rem / gm) * 8 + xcd;
-        split = blockIdx.y;
-        if (m_tile >= m_tiles || n_tile >= n_tiles) return;
+        const int per = (tm.whole + 7) >> 3;
+        int tile;
+        if (MODE == 2 && w >= 8 * per) {
+            const int q = w - 8 * per;   // the grid holds rem * rem_splits of these
+            tile = tm.whole + q % tm.rem;
+            split = q / tm.rem;
+            cut = (tile - tm.whole) * tm.rem_splits + split;
+            ksplit = tm.rem_ks;
+        } else {
+            tile = xcd * per + j;
+            split = MODE == 2 ? 0 : blockIdx.y;
+            if (tile >= tm.whole) return;
+        }
+        const int grp = tile / (tm.gm * tm.n_tiles);
+        const int rem = tile - grp * tm.gm * tm.n_tiles;
+        const int gsz = min(tm.gm, tm.m_tiles - grp * tm.gm);
+        m_tile = grp * tm.gm + rem % gsz;
+        n_tile = rem / gsz;
     }
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -659,7 +685,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
             for (int e = 0; e < 16; ++e) {
                 const int m = m0 + wm * TM + 32 * i + 8 * (e >> 2) + 4 * kh + (e & 3);
                 if (CHECKED && m >= M) continue;
-                if (SPLIT) {
+                if (MODE == 1) {
                     float* dst = p.partial + (static_cast<size_t>(split) * M + m) * Nw;
 #pragma unroll
                     for (int t = 0; t < NT; ++t)
@@ -684,6 +710,18 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
             }
         }
     };
+    if (MODE == 2 && cut >= 0) {   // the whole BM x BN tile, finished by finish_tiles_kernel
+        float* dst = p.partial + static_cast<size_t>(cut) * (BM * BN);
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int row = wm * TM + 32 * i + 8 * (e >> 2) + 4 * kh + (e & 3);
+#pragma unroll
+                for (int t = 0; t < NT; ++t) dst[row * BN + wn * TN + 32 * t + r32] = acc[i][t][e];
+            }
+        return;
+    }
     bool inside = m0 + BM <= M;
 #pragma unroll
     for (int t = 0; t < NT; ++t) inside = inside && nok[t];
@@ -691,31 +729,117 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
     else store_tile(std::true_type{});
 }
 
+// The remainder tiles of a MODE 2 launch: sum of each tile's K slices in
+// order, then the epilogue.  Workgroup (x, y): 16 rows of tile whole + x; a
+// thread owns 4 consecutive columns (SwiGLU: 4 gate columns and the matching
+// up columns, TN / 2 apart as the tile kernel's waves pair them).
+template <int BM, int BN, int TN, int EPI>
+__global__ void __launch_bounds__(256) finish_tiles_kernel(GemmArgs p, TileMap tm, int n0) {
+    constexpr int COLS = EPI == EPI_SWIGLU ? BN / 2 : BN;
+    const int tile = tm.whole + blockIdx.x;
+    const int grp = tile / (tm.gm * tm.n_tiles);
+    const int rem = tile - grp * tm.gm * tm.n_tiles;
+    const int gsz = min(tm.gm, tm.m_tiles - grp * tm.gm);
+    const int m0 = (grp * tm.gm + rem % gsz) * BM, c0 = n0 + (rem / gsz) * COLS;
+    const int n_out = EPI == EPI_SWIGLU ? p.F : p.Nw;
+    const float* base = p.partial + static_cast<size_t>(blockIdx.x) * tm.rem_splits * (BM * BN);
+    for (int idx = threadIdx.x; idx < 16 * COLS / 4; idx += 256) {
+        const int row = blockIdx.y * 16 + idx / (COLS / 4), c = 4 * (idx % (COLS / 4));
+        if (m0 + row >= p.M || c0 + c >= n_out) continue;   // n_out is a multiple of 4
+        const int b = EPI == EPI_SWIGLU ? c / (TN / 2) * TN + c % (TN / 2) : c;
+        auto sum = [&](const float* src) {
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            int z = 0;
+            for (; z + 4 <= tm.rem_splits; z += 4) {
+                f32x4 r[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) r[u] = *reinterpret_cast<const f32x4*>(src + (z + u) * (BM * BN));
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v += r[u];
+            }
+            for (; z < tm.rem_splits; ++z) v += *reinterpret_cast<const f32x4*>(src + z * (BM * BN));
+            return v;
+        };
+        const f32x4 v = sum(base + row * BN + b);
+        const size_t m = static_cast<size_t>(m0 + row);
+        if (EPI == EPI_F32) {
+            *reinterpret_cast<f32x4*>(p.out_f32 + m * p.ldo + c0 + c) = v;
+        } else if (EPI == EPI_RESID) {
+            f32x4* r = reinterpret_cast<f32x4*>(p.resid + m * p.ldr + c0 + c);
+            *r = *r + v;
+        } else {
+            const f32x4 u = sum(base + row * BN + b + TN / 2);
+            uint16_t o[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16(swiglu_bf16(v[e], u[e]));
+            *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.act) + m * p.ld_act + c0 + c) =
+                make_uint2(o[0] | static_cast<uint32_t>(o[1]) << 16, o[2] | static_cast<uint32_t>(o[3]) << 16);
+        }
+    }
+}
+
 template <int BM, int BN, int WM, int NW, int SA, int SW>
 hipError_t launch_dma128(const GemmArgs& a, const GemmPlan& p, int n0, int n1, hipStream_t s) {
-    const int m_tiles = (a.M + BM - 1) / BM;
+    TileMap tm{};
+    tm.m_tiles = (a.M + BM - 1) / BM;
     const int n_out = n1 - n0;
     const int bno = a.epi == EPI_SWIGLU ? BN / 2 : BN;
-    const int n_tiles = (n_out + bno - 1) / bno;
-    const int gm = m_tiles < 8 ? m_tiles : 8;
-    const int ntx = (n_tiles + 7) / 8;
-    const int groups = (m_tiles + gm - 1) / gm;
+    tm.n_tiles = (n_out + bno - 1) / bno;
+    tm.gm = tm.m_tiles < 8 ? tm.m_tiles : 8;
+    tm.whole = tm.m_tiles * tm.n_tiles;
     // split-K counts that are multiples of 8: one split per XCD (see the kernel)
-    const int xsplit = p.splits >= 8 && p.splits % 8 == 0;
-    const dim3 grid = xsplit ? dim3(8 * m_tiles * n_tiles, p.splits / 8) : dim3(8 * ntx * groups * gm, p.splits);
+    tm.xsplit = p.splits >= 8 && p.splits % 8 == 0;
     const dim3 block(64 * NW);
+    const dim3 grid = tm.xsplit ? dim3(8 * tm.whole, p.splits / 8) : dim3((tm.whole + 7) / 8 * 8, p.splits);
+#define RL_DMA(EPI, MODE) \
+    hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, WM, NW, SA, SW, EPI, MODE>), grid, block, 0, s, a, p.ksplit, tm, n0)
     if (p.splits > 1) {
-        if (a.epi == EPI_SWIGLU)
-            hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, WM, NW, SA, SW, EPI_SWIGLU, true>), grid, block, 0, s, a, p.ksplit, m_tiles, n_tiles, n0, gm, xsplit);
-        else
-            hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, WM, NW, SA, SW, EPI_F32, true>), grid, block, 0, s, a, p.ksplit, m_tiles, n_tiles, n0, gm, xsplit);
+        if (a.epi == EPI_SWIGLU) RL_DMA(EPI_SWIGLU, 1);
+        else RL_DMA(EPI_F32, 1);
     } else if (a.epi == EPI_F32) {
-        hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, WM, NW, SA, SW, EPI_F32, false>), grid, block, 0, s, a, p.ksplit, m_tiles, n_tiles, n0, gm, 0);
+        RL_DMA(EPI_F32, 0);
     } else if (a.epi == EPI_RESID) {
-        hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, WM, NW, SA, SW, EPI_RESID, false>), grid, block, 0, s, a, p.ksplit, m_tiles, n_tiles, n0, gm, 0);
+        RL_DMA(EPI_RESID, 0);
     } else {
-        hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, WM, NW, SA, SW, EPI_SWIGLU, false>), grid, block, 0, s, a, p.ksplit, m_tiles, n_tiles, n0, gm, 0);
+        RL_DMA(EPI_SWIGLU, 0);
     }
+#undef RL_DMA
+    return hipGetLastError();
+}
+
+// 256 x 256 tiles, whole rounds of them over the CUs and the remainder cut in
+// K so that it fills one more (shorter) round; its slices are summed by
+// finish_tiles_kernel.
+hipError_t launch_cut256(const GemmArgs& a, hipStream_t s) {
+    constexpr int BM = 256, BN = 256, WM = 2, NW = 8, TN = BN / (NW / WM);
+    TileMap tm{};
+    tm.m_tiles = (a.M + BM - 1) / BM;
+    const int n_out = a.epi == EPI_SWIGLU ? a.F : a.Nw;
+    const int bno = a.epi == EPI_SWIGLU ? BN / 2 : BN;
+    tm.n_tiles = (n_out + bno - 1) / bno;
+    tm.gm = tm.m_tiles < 8 ? tm.m_tiles : 8;
+    const int tiles = tm.m_tiles * tm.n_tiles;
+    const RemainderCut c = remainder_cut(tiles, a.K);
+    if (c.splits <= 1) {
+        GemmPlan q{};
+        q.splits = 1;
+        q.ksplit = a.K;
+        return launch_dma128<256, 256, 2, 8, 2, 3>(a, q, 0, n_out, s);
+    }
+    tm.whole = tiles - c.tiles;
+    tm.rem = c.tiles;
+    tm.rem_splits = c.splits;
+    tm.rem_ks = c.ks;
+    const dim3 grid((tm.whole + 7) / 8 * 8 + tm.rem * tm.rem_splits), block(64 * NW), fgrid(tm.rem, BM / 16);
+#define RL_CUT(EPI)                                                                                                   \
+    do {                                                                                                              \
+        hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, WM, NW, 2, 3, EPI, 2>), grid, block, 0, s, a, a.K, tm, 0);      \
+        hipLaunchKernelGGL((finish_tiles_kernel<BM, BN, TN, EPI>), fgrid, dim3(256), 0, s, a, tm, 0);                  \
+    } while (0)
+    if (a.epi == EPI_F32) RL_CUT(EPI_F32);
+    else if (a.epi == EPI_RESID) RL_CUT(EPI_RESID);
+    else RL_CUT(EPI_SWIGLU);
+#undef RL_CUT
     return hipGetLastError();
 }
 
@@ -774,6 +898,9 @@ hipError_t launch_tile_variant(int variant, const GemmArgs& a, const GemmPlan& p
         case kDmaVariant256x256: return launch_dma<256, 256, 2, 8, 5>(a, p, n0, n1, s);
         case kDmaVariant128x256: return launch_dma<128, 256, 2, 8, 6>(a, p, n0, n1, s);
         case kLineVariant256x256: return launch_dma128<256, 256, 2, 8, 2, 3>(a, p, n0, n1, s);
+        case kLineVariant256x256Cut:   // whole outputs only
+            if (n0 != 0 || p.splits > 1) return hipErrorInvalidValue;
+            return launch_cut256(a, s);
         case kLineVariant128x128: return launch_dma128<128, 128, 2, 4, 2, 3>(a, p, n0, n1, s);
         case kLineVariant128x256: return launch_dma128<128, 256, 2, 8, 3, 3>(a, p, n0, n1, s);
         case kLineVariant128x128Deep: return launch_dma128<128, 128, 2, 4, 4, 4>(a, p, n0, n1, s);

@@ -134,6 +134,13 @@ constexpr int kLineVariant128x256 = 9;      // direct-to-LDS, 128-byte rows, 128
 constexpr int kLineVariant128x128Deep = 10; // direct-to-LDS, 128-byte rows, 128 x 128, 4 waves, 4-stage ring
 constexpr int kGemvVariant = 11;            // M <= 32: 16 weight rows x all K per 8-wave workgroup, no split-K
 constexpr int kGemvWideVariant = 12;        // M <= 64: 64 weight rows x a K slice per 4-wave workgroup
+constexpr int kLineVariant256x256Cut = 13; // kLineVariant256x256, the tiles past whole rounds cut in K
+
+constexpr int kCUs = 256;
+// How the tiles past the whole rounds of one 256 x 256 tile per CU are cut: the
+// last `tiles` of them into `splits` K slices of ks (splits <= 1: not cut).
+struct RemainderCut { int tiles, splits, ks; };
+RemainderCut remainder_cut(int tiles, int K);
 
 constexpr int kMaxSplits = 32;
 constexpr size_t kPartCapFloats = size_t(32) << 20;   // split-K partials budget
