@@ -751,6 +751,10 @@ rl_status run_moe(rl_decode_ctx* c, int l, int n, const void* h) {
     return RL_OK;
 }
 
+// Scoring passes of more LM-head rows than this reduce the logits inside the
+// head's 256 x 256 tiles; fewer go through the decode kernels and a logits buffer.
+constexpr int kFusedHeadRows = 128;
+
 rl_status run_forward(rl_decode_ctx* c, const Fwd& f) {
     const rl_model_config& cf = c->cfg;
     const Layout& L = c->lay;
@@ -864,6 +868,33 @@ rl_status run_forward(rl_decode_ctx* c, const Fwd& f) {
         e = launch_rmsnorm(dt, x, f.final_sel, nf, H, c->w.final_norm, eps, h, c->stream);
         if (e != hipSuccess) return hip_fail(c, e, "final rmsnorm launch");
         pr.done(nf * H * (4.0 + es) + H * es, 0.0);
+    }
+    if (f.score_items && c->bf16() && H % 64 == 0 && nf > kFusedHeadRows) {
+        // rows whose column tiles (one float2 per row and kLseCols logits) fit the split-K partials
+        const int V = cf.vocab, n_tiles = ceil_div(V, kLseCols);
+        const size_t fit = L.part_floats / 2 / n_tiles;
+        const size_t addr = 0xFFFFFFFFull / (2 * static_cast<size_t>(H));   // the GEMM's 32-bit row offsets
+        const int step = static_cast<int>(std::min<size_t>({fit, addr, size_t(1) << 20})) / 256 * 256;
+        for (int r0 = 0; r0 < nf; r0 += step) {
+            const int nc = std::min(step, nf - r0);
+            const uint8_t* hr = static_cast<const uint8_t*>(h) + static_cast<size_t>(r0) * H * esz;
+            GemmArgs a{};
+            a.A = hr; a.lda = H; a.W = c->w.lm_head; a.ldw = H; a.M = nc; a.Nw = V; a.K = H; a.epi = EPI_LSE;
+            a.lse = c->wsp<float2>(L.off_part);
+            a.T = f.T;
+            {
+                Prof pr(c, RL_K_GEMM_LM_HEAD);
+                e = launch_gemm_lse(a, c->stream);
+                if (e != hipSuccess) return hip_fail(c, e, "scoring head launch");
+                pr.done(es * V * H + es * nc * H + 8.0 * nc * n_tiles, 2.0 * nc * V * H);
+            }
+            Prof pr(c, RL_K_SAMPLE);
+            e = launch_logprob_lse(a.lse, n_tiles, nc, hr, c->w.lm_head, H, V, f.score_items + r0, f.score_idx,
+                                   f.score_targets, f.T, f.out_logp, c->stream);
+            if (e != hipSuccess) return hip_fail(c, e, "log-prob launch");
+            pr.done(8.0 * nc * n_tiles + 4.0 * nc * H, 0.0);
+        }
+        return RL_OK;
     }
     if (f.score_items) {   // LM head and log-probabilities in chunks of score_chunk rows
         const int V = cf.vocab;

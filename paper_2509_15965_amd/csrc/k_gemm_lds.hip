@@ -737,6 +737,77 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
             }
         return;
     }
+    if constexpr (EPI == EPI_LSE) {
+        // (max, sum-exp) of every row over the tile's columns.  32 rows at a
+        // time go through LDS (the ring is free by then) so that two lanes
+        // hold a row's 64 columns of this wave; the four waves of a row meet
+        // in LDS.  About 4% of a tile of K 3584, against 13% for storing the
+        // tile's logits and 8% for reading them back.
+        static_assert(NT == 2 && WN == 4 && BN == kLseCols, "row reduction layout");
+        constexpr int LDZ = 68;   // floats per row: 16-byte aligned, reads free of bank conflicts
+        static_assert(NW * 32 * LDZ * 4 + WN * BM * 8 <= SA * ASTAGE + SW * BSTAGE, "LDS");
+        float* zs = reinterpret_cast<float*>(smem) + wave * 32 * LDZ;
+        float2* part = reinterpret_cast<float2*>(smem + NW * 32 * LDZ * 4);   // [WN][BM]
+        const int c0 = n_tile * BN + wn * TN + (lane & 1) * 32;   // this lane's 32 columns
+        __syncthreads();   // every wave is done with the ring
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    zs[(8 * (e >> 2) + 4 * kh + (e & 3)) * LDZ + 32 * t + r32] = acc[i][t][e];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const float* zr = zs + (lane >> 1) * LDZ + (lane & 1) * 32;
+            f32x4 z[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) z[q] = *reinterpret_cast<const f32x4*>(zr + 4 * q);
+            if (p.T != 1.0f) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) z[q][e] /= p.T;
+            }
+            if (c0 + 32 > Nw) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (c0 + 4 * q + e >= Nw) z[q][e] = -INFINITY;
+            }
+            float m = -INFINITY;
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) m = fmaxf(m, z[q][e]);
+            m = fmaxf(m, __shfl_xor(m, 1, 64));
+            const float m_use = fabsf(m) == INFINITY ? 0.0f : m;   // no finite entry to shift by
+            float s = 0.0f;
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s += __expf(z[q][e] - m_use);
+            s += __shfl_xor(s, 1, 64);
+            if ((lane & 1) == 0) part[wn * BM + wm * TM + 32 * i + (lane >> 1)] = make_float2(m, s);
+            __builtin_amdgcn_wave_barrier();   // zs is rewritten for the next 32 rows
+        }
+        __syncthreads();
+        for (int row = tid; row < BM; row += 64 * NW) {
+            if (m0 + row >= M) continue;
+            float2 v[WN];
+#pragma unroll
+            for (int q = 0; q < WN; ++q) v[q] = part[q * BM + row];
+            float m = v[0].x;
+#pragma unroll
+            for (int q = 1; q < WN; ++q) m = fmaxf(m, v[q].x);
+            float s = 0.0f;
+#pragma unroll
+            for (int q = 0; q < WN; ++q) s += v[q].x == m ? v[q].y : v[q].y * __expf(v[q].x - m);
+            p.lse[static_cast<size_t>(n_tile) * M + m0 + row] = make_float2(m, s);
+        }
+        return;
+    }
     bool inside = m0 + BM <= M;
 #pragma unroll
     for (int t = 0; t < NT; ++t) inside = inside && nok[t];
@@ -926,6 +997,23 @@ hipError_t launch_tile_variant(int variant, const GemmArgs& a, const GemmPlan& p
 }
 
 }  // namespace
+
+hipError_t launch_gemm_lse(const GemmArgs& a, hipStream_t s) {
+    if (a.M <= 0) return hipSuccess;
+    constexpr int BM = 256, BN = kLseCols, NW = 8;
+    constexpr uint64_t kOffLimit = 0xFFFFFFFFull;
+    if (a.K % 64 != 0 || !(a.T > 0.0f) || static_cast<uint64_t>(a.Nw) * a.ldw * 2 > kOffLimit ||
+        static_cast<uint64_t>(a.M) * a.lda * 2 > kOffLimit)
+        return hipErrorInvalidValue;
+    TileMap tm{};
+    tm.m_tiles = (a.M + BM - 1) / BM;
+    tm.n_tiles = (a.Nw + BN - 1) / BN;
+    tm.gm = tm.m_tiles < 8 ? tm.m_tiles : 8;
+    tm.whole = tm.m_tiles * tm.n_tiles;
+    hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, 2, NW, 2, 3, EPI_LSE, 0>), dim3((tm.whole + 7) / 8 * 8),
+                       dim3(64 * NW), 0, s, a, a.K, tm, 0);
+    return hipGetLastError();
+}
 
 static hipError_t launch_segments(const GemmArgs& a, const GemmPlan& p, hipStream_t s) {
     const int n_out = a.epi == EPI_SWIGLU ? a.F : a.Nw;

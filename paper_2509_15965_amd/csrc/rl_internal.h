@@ -55,7 +55,8 @@ __device__ __forceinline__ size_t kv_block(const KvPages& kp, int layer, int Hkv
 enum Epi {
     EPI_F32 = 0,      // store fp32 Y
     EPI_RESID = 1,    // fp32 residual += Y
-    EPI_SWIGLU = 2    // act[m][c] = storage(silu(Y[m][c]) * Y[m][F + c]), c < F
+    EPI_SWIGLU = 2,   // act[m][c] = storage(silu(Y[m][c]) * Y[m][F + c]), c < F
+    EPI_LSE = 3       // lse[tile][m] = (max, sum exp(. - max)) of Y[m][c] / T over a column tile
 };
 
 // One split-KV attention work item: a block of nq consecutive query tokens
@@ -92,7 +93,14 @@ struct GemmArgs {
     void* act;       int ld_act;  // EPI_SWIGLU output, model dtype
     int F;                        // EPI_SWIGLU
     float* partial;               // [splits][M][Nw] when splits > 1
+    float2* lse;                  // EPI_LSE: [column tiles of kLseCols][M]
+    float T;                      // EPI_LSE: temperature (> 0)
 };
+
+// Scoring head: logits are reduced to one (max, sum-exp) per row and kLseCols
+// columns inside the GEMM (launch_gemm_lse) and never written;
+// launch_logprob_lse merges them and computes each target's logit itself.
+constexpr int kLseCols = 256;
 
 // Mixture of experts: one grouped expert projection (k_moe.hip).
 constexpr int kMoeMaxExperts = 1024;
@@ -246,6 +254,13 @@ constexpr int kSampleMaxChunks = 64;
 hipError_t launch_logprob(const float* logits, int ld, int n_rows, int V, const int32_t* row_items,
                           const int32_t* item_idx, const int32_t* targets, float T, float* out,
                           hipStream_t s);
+
+hipError_t launch_gemm_lse(const GemmArgs& a, hipStream_t s);   // bf16, K % 64 == 0, operands under 4 GiB
+// The same values as launch_logprob from the column tiles of launch_gemm_lse
+// ([n_tiles][n_rows]): h [n_rows][H] and w [V][H] are the head's operands.
+hipError_t launch_logprob_lse(const float2* lse, int n_tiles, int n_rows, const void* h, const void* w, int H, int V,
+                              const int32_t* row_items, const int32_t* item_idx, const int32_t* targets, float T,
+                              float* out, hipStream_t s);
 
 // SampleParts a launch over n rows of V logits writes (0: a single chunk per
 // row, no partials).

@@ -1,0 +1,45 @@
+"""The scoring head that reduces logits inside its GEMM tiles (more than 128 head rows) against the one that
+writes them (each sequence scored alone), on the same hidden states."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_15965_amd.configs import ModelShape
+from paper_2509_15965_amd.inputs import make_weights
+from paper_2509_15965_amd.rl_decode import RL_GEMM_T128, RL_OPT_GEMM_PLAN, Engine, gemm_plan_code
+
+pytestmark = pytest.mark.gpu
+
+
+def score(eng, prompts, group, resp, T):
+    po = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int32)
+    ro = np.concatenate([[0], np.cumsum([len(r) for r in resp])]).astype(np.int32)
+    out = torch.empty(int(ro[-1]), device="cuda")
+    i32 = lambda a: torch.as_tensor(np.concatenate(a), dtype=torch.int32, device="cuda")
+    eng.score(list(range(len(resp))), po, i32(prompts), ro, i32(resp), out, group=group, temperature=T)
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+# head rows 129 (just past the line), 256 (a whole row tile), 257 and 600; vocabularies of one ragged column tile, whole
+# tiles and a ragged last one
+@pytest.mark.parametrize("vocab,rlens,T", [(200, [65, 65, 1, 1], 1.0), (512, [64, 64, 64, 66], 0.6), (1032, [64, 64, 64, 67], 0.0),
+                                           (1288, [100, 120, 40, 90, 110, 128], 0.6)])
+def test_head_in_tiles(vocab, rlens, T):
+    shape = ModelShape(1, 256, 4, 2, 64, 512, vocab, 1e-6, 1e4, "bf16")
+    w = make_weights(shape, 9, device="cuda", init="fanin")
+    w["lm_head"][min(vocab - 1, 130)] *= 12   # one entry far above the rest: a column tile that dominates the sum
+    rng = np.random.default_rng(vocab)
+    group = 2
+    prompts = [rng.integers(0, vocab, 9).astype(np.int32) for _ in range(len(rlens) // group)]
+    resp = [rng.integers(0, vocab, m).astype(np.int32) for m in rlens]
+    resp[0][3], resp[1][0] = -1, vocab   # not scored: NaN
+    eng = Engine(shape, w, max_seqs=len(rlens), max_ctx=160, max_prefill_tokens=1024)
+    # one tile kernel for every row count: the hidden states are then the same bits in both calls
+    eng.set_option(RL_OPT_GEMM_PLAN, gemm_plan_code(RL_GEMM_T128))
+    together = score(eng, prompts, group, resp, T)
+    alone = np.concatenate([score(eng, [prompts[i // group]], 1, [resp[i]], T) for i in range(len(resp))])
+    eng.close()
+    assert np.array_equal(np.isnan(together), np.isnan(alone)) and np.isnan(alone).sum() == 2
+    # fp32 sums in another order: logits of |z| < 64 and their LSE, each a few units of 2^-24 relative, over T
+    np.testing.assert_allclose(together[~np.isnan(alone)], alone[~np.isnan(alone)], rtol=0, atol=64 * 2.0 ** -21)
