@@ -446,7 +446,8 @@ struct TileMap {
 };
 
 // MODE 0: whole tiles with the epilogue; 1: split-K, partial tiles [split][M][Nw];
-// 2: whole tiles with the epilogue and a K-cut remainder (TileMap::rem)
+// 2: whole tiles with the epilogue and a K-cut remainder (TileMap::rem); 3: the
+// experts' row tiles of a mixture of experts (GemmArgs::g_*)
 template <int BM, int BN, int WM, int NW, int SA, int SW, int EPI, int MODE>
 __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ksplit, TileMap tm, int n0) {
     constexpr int BK = 64, ROWB = 128;
@@ -466,7 +467,25 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
     const int xcd = w & 7, j = w >> 3;
     int m_tile, n_tile, split;
     int cut = -1;   // MODE 2: partial tile written by a remainder workgroup
-    if (tm.xsplit) {
+    int row0 = 0, M = p.M;   // MODE 3: the expert's pair positions [row0, M)
+    const uint16_t* W = static_cast<const uint16_t*>(p.W);
+    if (MODE == 3) {
+        // an expert's tiles are consecutive, row tiles fastest, so the row
+        // tiles that share a weight tile run together; tiles are counted on
+        // the device and shared out equally over the XCDs
+        const int total = p.g_toff[p.g_E] * tm.n_tiles, per = (total + 7) >> 3;
+        const int tile = xcd * per + j;
+        if (j >= per || tile >= total) return;
+        const int e = __builtin_amdgcn_readfirstlane(min(max(p.g_tiles[tile / tm.n_tiles], 0), p.g_E - 1));
+        const int t0 = p.g_toff[e], mc = max(p.g_toff[e + 1] - t0, 1);
+        const int local = tile - t0 * tm.n_tiles;
+        m_tile = local % mc;
+        n_tile = local / mc;
+        split = 0;
+        row0 = min(max(p.g_off[e], 0), p.g_npairs - 1);
+        M = min(max(p.g_off[e + 1], row0 + 1), p.g_npairs);
+        W += static_cast<size_t>(e) * p.g_wstride;
+    } else if (tm.xsplit) {
         // split-K over the XCDs: XCD x % 8 runs split 8y + x % 8 of every tile
         // (M tiles fastest), so its K range of the activations stays in its L2
         // and the M tiles of one weight tile run back to back
@@ -499,8 +518,8 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int r32 = lane & 31, kh = lane >> 5;
-    const int M = p.M, Nw = p.Nw, K = p.K;
-    const int m0 = m_tile * BM;
+    const int Nw = p.Nw, K = p.K;
+    const int m0 = row0 + m_tile * BM;
 
     auto wrow = [&](int b, bool* ok) -> int {
         if (EPI == EPI_SWIGLU) {
@@ -521,7 +540,6 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
     const int nk = (ke - kb) / BK;
 
     const uint16_t* A = static_cast<const uint16_t*>(p.A);
-    const uint16_t* W = static_cast<const uint16_t*>(p.W);
     // DMA lane l of block g: row 8g + l/8, LDS chunk l%8 <- source chunk (l%8) ^ ((row/2)%8)
     const int lrow = lane >> 3;
     uint32_t aoff[AQ], boff[BQ];   // byte offsets (the launcher keeps them below 4 GiB)
@@ -530,6 +548,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
         const int g = wave * AQ + q;
         int m = m0 + 8 * g + lrow;
         m = m < M ? m : M - 1;
+        if (MODE == 3 && EPI == EPI_SWIGLU) m = min(max(p.g_pairs[m], 0), p.g_npairs - 1) / p.g_k;   // the pair's token row
         const int ch = (lane & 7) ^ (((8 * g + lrow) >> 1) & 7);
         aoff[q] = 2u * (static_cast<uint32_t>(m) * static_cast<uint32_t>(p.lda) + 8u * ch);
     }
@@ -541,6 +560,15 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
         n = ok ? n : 0;
         const int ch = (lane & 7) ^ (((8 * g + lrow) >> 1) & 7);
         boff[q] = 2u * (static_cast<uint32_t>(n) * static_cast<uint32_t>(p.ldw) + 8u * ch);
+    }
+    // MODE 3, down: the plane row and routing weight of the tile's row tid
+    int prow = 0;
+    float pwt = 0.0f;
+    if (MODE == 3 && EPI == EPI_RESID && tid < BM && m0 + tid < M) {
+        const int pr = min(max(p.g_pairs[m0 + tid], 0), p.g_npairs - 1);
+        const int row = pr / p.g_k;
+        prow = (pr - row * p.g_k) * p.g_rows + row;
+        pwt = p.g_pw[pr];
     }
     uint8_t* const abuf = smem;
     uint8_t* const bbuf = smem + SA * ASTAGE;
@@ -675,6 +703,32 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
     bool nok[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) nrow[t] = wrow(wn * TN + 32 * t + r32, &nok[t]);
+    if constexpr (MODE == 3 && EPI == EPI_RESID) {
+        // weighted rows to their planes; where each row goes is in LDS (the ring is free)
+        static_assert(64 * NW >= BM, "one row per thread");
+        int* rows = reinterpret_cast<int*>(smem);
+        float* wts = reinterpret_cast<float*>(smem) + BM;
+        __syncthreads();
+        if (tid < BM) {
+            rows[tid] = prow;
+            wts[tid] = pwt;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int r = wm * TM + 32 * i + 8 * (e >> 2) + 4 * kh + (e & 3);
+                if (m0 + r >= M) continue;
+                float* dst = p.g_plane + static_cast<size_t>(rows[r]) * Nw;
+                const float wt = wts[r];
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    if (nok[t]) dst[nrow[t]] = wt * acc[i][t][e];
+            }
+        }
+        return;
+    }
     // CHECKED: per-element row and column bounds (edge tiles); interior tiles
     // store without them
     auto store_tile = [&](auto checked) {
@@ -997,6 +1051,54 @@ hipError_t launch_tile_variant(int variant, const GemmArgs& a, const GemmPlan& p
 }
 
 }  // namespace
+
+// The experts' projections in tiles, or in the GEMV form (launch_moe_gemv).
+// Both are bound by the stream of the experts' weights while an expert has few
+// pairs; the tiles' DMA ring streams them a little faster from 2 pairs per
+// expert on (128 experts of 768, hidden 2048, both projections: 32 rows 232 ->
+// 221 us, 131 rows 283 -> 251), and below the GEMV form's smaller workgroups
+// spread the few experts reached better (8 rows: 102 against 111).  Past 64
+// pairs the GEMV form re-reads the weights from L2 for every 64 pairs (12800
+// rows: 4627 -> 1400 us).  256-row tiles are the faster ones once they are
+// mostly full (30000 rows: 2938 -> 2685 us; 12800: 1400 -> 1437).
+constexpr int kMoeTilePairs = 2;        // mean pairs per expert from which tiles are used
+constexpr int kMoeTile256Pairs = 1024;  // and from which they hold 256 pairs
+bool moe_tiles_fit(int npairs, int n_rows, int E, int H, int Fe, int* bm) {
+    constexpr uint64_t kOffLimit = 0xFFFFFFFFull;
+    if (H % 64 != 0 || Fe % 64 != 0) return false;
+    if (static_cast<uint64_t>(n_rows) * H * 2 > kOffLimit || static_cast<uint64_t>(npairs) * Fe * 2 > kOffLimit ||
+        static_cast<uint64_t>(2) * Fe * H * 2 > kOffLimit)
+        return false;
+    const int avg = npairs / E;
+    if (avg < kMoeTilePairs) return false;
+    *bm = avg < kMoeTile256Pairs ? 128 : 256;
+    return true;
+}
+
+hipError_t launch_moe_tiles(const MoeArgs& a, int epi, hipStream_t s) {
+    if (a.npairs <= 0) return hipSuccess;
+    if (a.K % 64 != 0 || (a.bm != 128 && a.bm != 256)) return hipErrorInvalidValue;
+    GemmArgs g{};
+    g.A = a.A; g.lda = a.lda; g.W = a.W; g.ldw = a.ldw; g.M = a.npairs; g.Nw = a.Nw; g.K = a.K; g.epi = epi;
+    g.act = a.act; g.ld_act = a.ld_act; g.F = a.F;
+    g.g_off = a.off; g.g_toff = a.toff; g.g_tiles = a.tiles; g.g_pairs = a.pairs; g.g_pw = a.pw; g.g_plane = a.plane;
+    g.g_wstride = a.w_expert; g.g_E = a.E; g.g_k = a.k; g.g_rows = a.n_rows; g.g_npairs = a.npairs;
+    TileMap tm{};
+    tm.n_tiles = epi == EPI_SWIGLU ? (a.F + 127) / 128 : (a.Nw + 255) / 256;
+    // at most one part-filled row tile per expert with any pair
+    const int m_tiles = a.npairs / a.bm + (a.npairs < a.E ? a.npairs : a.E);
+    const dim3 grid((m_tiles * tm.n_tiles + 7) / 8 * 8), block(512);
+#define RL_MOE(BM, SA, EPI) hipLaunchKernelGGL((gemm_dma128_kernel<BM, 256, 2, 8, SA, 3, EPI, 3>), grid, block, 0, s, g, a.K, tm, 0)
+    if (a.bm == 256) {
+        if (epi == EPI_SWIGLU) RL_MOE(256, 2, EPI_SWIGLU);
+        else RL_MOE(256, 2, EPI_RESID);
+    } else {
+        if (epi == EPI_SWIGLU) RL_MOE(128, 3, EPI_SWIGLU);
+        else RL_MOE(128, 3, EPI_RESID);
+    }
+#undef RL_MOE
+    return hipGetLastError();
+}
 
 hipError_t launch_gemm_lse(const GemmArgs& a, hipStream_t s) {
     if (a.M <= 0) return hipSuccess;

@@ -78,7 +78,8 @@ __global__ void __launch_bounds__(256) moe_topk_kernel(const float* __restrict__
 // Pairs grouped by expert (one workgroup): counts, an exclusive scan, then
 // each pair's slot in its expert's range.
 __global__ void __launch_bounds__(1024) moe_group_kernel(const int32_t* __restrict__ ids, int npairs, int E,
-                                                         int32_t* __restrict__ off, int32_t* __restrict__ pairs) {
+                                                         int32_t* __restrict__ off, int32_t* __restrict__ pairs, int bm,
+                                                         int32_t* __restrict__ toff, int32_t* __restrict__ tiles) {
     __shared__ int32_t cnt[kMoeMaxExperts];
     __shared__ int32_t scan[kMoeMaxExperts];
     const int t = threadIdx.x;
@@ -98,9 +99,26 @@ __global__ void __launch_bounds__(1024) moe_group_kernel(const int32_t* __restri
         scan[t] += add;
         __syncthreads();
     }
-    const int base = scan[t] - cnt[t];   // exclusive
+    const int mine = cnt[t];
+    const int base = scan[t] - mine;   // exclusive
     if (t < E) off[t] = base;
     if (t == E - 1) off[E] = scan[t];
+    if (bm > 0) {   // row tiles of bm pairs, expert by expert
+        const int nt = (mine + bm - 1) / bm;   // 0 for t >= E
+        __syncthreads();
+        scan[t] = nt;
+        __syncthreads();
+        for (int d = 1; d < kMoeMaxExperts; d <<= 1) {
+            const int add = t >= d ? scan[t - d] : 0;
+            __syncthreads();
+            scan[t] += add;
+            __syncthreads();
+        }
+        const int tb = scan[t] - nt;
+        if (t < E) toff[t] = tb;
+        if (t == E - 1) toff[E] = scan[t];
+        for (int i = 0; i < nt; ++i) tiles[tb + i] = t;
+    }
     __syncthreads();
     cnt[t] = base;   // next free slot of expert t
     __syncthreads();
@@ -218,11 +236,12 @@ __global__ void __launch_bounds__(256) moe_gemv_kernel(MoeArgs a, int kw) {
 }  // namespace
 
 hipError_t launch_moe_route(const float* logits, int n, int E, int k, int32_t* ids, float* w, int32_t* off,
-                            int32_t* pairs, hipStream_t s) {
+                            int32_t* pairs, int bm, int32_t* toff, int32_t* tiles, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     if (E < 1 || E > kMoeMaxExperts || k < 1 || k > E || k > kMoeMaxTopK) return hipErrorInvalidValue;
     hipLaunchKernelGGL(moe_topk_kernel, dim3((n + 3) / 4), dim3(256), 0, s, logits, n, E, k, ids, w);
-    hipLaunchKernelGGL(moe_group_kernel, dim3(1), dim3(1024), 0, s, ids, n * k, E, off, pairs);
+    hipLaunchKernelGGL(moe_group_kernel, dim3(1), dim3(1024), 0, s, ids, n * k, E, off, pairs, bm, toff,
+                       tiles);
     return hipGetLastError();
 }
 

@@ -95,6 +95,16 @@ struct GemmArgs {
     float* partial;               // [splits][M][Nw] when splits > 1
     float2* lse;                  // EPI_LSE: [column tiles of kLseCols][M]
     float T;                      // EPI_LSE: temperature (> 0)
+    // grouped expert projection (launch_moe_tiles): A rows are gathered and
+    // the outputs placed as launch_moe_gemv does
+    const int32_t* g_off;         // [g_E + 1] ranges of pairs per expert
+    const int32_t* g_toff;        // [g_E + 1] first row tile of every expert
+    const int32_t* g_tiles;       // expert of every row tile
+    const int32_t* g_pairs;
+    const float* g_pw;
+    float* g_plane;
+    size_t g_wstride;
+    int g_E, g_k, g_rows, g_npairs;
 };
 
 // Scoring head: logits are reduced to one (max, sum-exp) per row and kLseCols
@@ -116,6 +126,9 @@ struct MoeArgs {
     const float* pw;                       // [n*k] routing weight of pair p (down only)
     uint16_t* act; int ld_act;             // gate|up output: SwiGLU row of each pair position
     float* plane;                          // down output: [k][n_rows][Nw], plane j of row `row`
+    const int32_t* toff;                   // [E + 1] row tiles (bm pairs each) before every expert's (launch_moe_tiles)
+    const int32_t* tiles;                  // expert of every row tile, at most npairs / bm + E of them
+    int bm;                                // rows of a row tile: 128 or 256
 };
 
 struct GemmPlan {
@@ -204,9 +217,14 @@ hipError_t launch_attention_bf16(const AttnItem* items, int n_items, const void*
                                  hipStream_t s, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 
 // Router logits [n][E] -> each row's top k experts and weights ([n][k]),
-// then the n * k pairs grouped by expert (off [E + 1], pairs [n * k]).
+// then the n * k pairs grouped by expert (off [E + 1], pairs [n * k]) and,
+// with bm > 0, cut into row tiles of bm pairs (toff [E + 1], tiles).
 hipError_t launch_moe_route(const float* logits, int n, int E, int k, int32_t* ids, float* w, int32_t* off,
-                            int32_t* pairs, hipStream_t s);
+                            int32_t* pairs, int bm, int32_t* toff, int32_t* tiles, hipStream_t s);
+// The same projection as launch_moe_gemv in MFMA tiles of bm pairs x 256 weight
+// rows (K a multiple of 64; activations and one expert's weights under 4 GiB).
+hipError_t launch_moe_tiles(const MoeArgs& a, int epi, hipStream_t s);
+bool moe_tiles_fit(int npairs, int n_rows, int E, int H, int Fe, int* bm);   // whether, and with which bm, a layer takes them
 // One grouped expert projection (epi: EPI_SWIGLU for gate|up, EPI_RESID for
 // down, which writes routing-weighted planes).
 hipError_t launch_moe_gemv(const MoeArgs& a, int epi, hipStream_t s);
