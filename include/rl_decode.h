@@ -408,8 +408,8 @@ rl_status rl_decode_rebind(rl_decode_ctx* ctx, const rl_weights* w, void* kv_poo
 typedef enum rl_option {
     RL_OPT_ATTN_CHUNK = 1,   /* positions per split-KV chunk: 0 = automatic
                                 (decode steps that read shared prompts: 256;
-                                other decode steps: the largest power of two
-                                that still gives about 1024 work items;
+                                other decode steps: all rows' keys cut into
+                                about 1024 equal runs over the kv-heads;
                                 prefill and scoring: 1024), else a multiple of
                                 32 in [32, 65536]; doubled as needed so no
                                 sequence has more than 64 chunks and the work

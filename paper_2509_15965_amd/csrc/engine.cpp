@@ -23,7 +23,7 @@ constexpr uint32_t kMagic = 0x524C4443u;   // "RLDC"
 constexpr uint32_t kDead = 0xDEADDEADu;
 constexpr int kStages = 3;                  // pinned metadata staging ring
 constexpr int kPartItems = 8192;            // split-KV partial slots per call
-constexpr int kAttnWaveTarget = 1024;       // split-KV: keep about one wave per SIMD, each as long as possible
+constexpr int kAttnWaveTarget = 1024;       // decode attention: one wave per SIMD
 constexpr int kSharedDecodeChunk = 256;     // split-KV keys per item in decode steps that read shared prompts
 constexpr int kPrefillChunk = 1024;         // default keys per prefill work item
 constexpr int kNoAllocMaxRows = 1 << 20;    // rows of one rl_sample_logits_noalloc call
@@ -523,7 +523,8 @@ struct Fwd {
     const int32_t* dst_slots = nullptr;
     const int32_t* row_slot = nullptr;      // fp32 attention: slot each row reads
     const AttnItem* items = nullptr;
-    int n_items = 0;
+    const int32_t* wave_first = nullptr;    // first item of every wave (nullptr: one item each)
+    int n_waves = 0;
     int n_partial_items = 0;
     const PrefillTile* tiles = nullptr;     // prefill / scoring: shared-LDS tiles instead of items
     int n_tiles = 0;
@@ -825,7 +826,7 @@ rl_status run_forward(rl_decode_ctx* c, const Fwd& f) {
                 e = launch_attention_prefill(f.tiles, f.n_tiles, q, c->kslab(), c->vslab(), f.kvp, Hq, Hkv, D,
                                              l, attn, c->stream);
             else if (c->bf16())
-                e = launch_attention_bf16(f.items, f.n_items, q, c->kslab(), c->vslab(), f.kvp, Hq, Hkv,
+                e = launch_attention_bf16(f.items, f.wave_first, f.n_waves, q, c->kslab(), c->vslab(), f.kvp, Hq, Hkv,
                                           D, l, attn, apart, c->stream, pr.start(), pr.stop());
             else
                 e = launch_attention_f32(n, f.row_slot, f.row_pos, static_cast<const float*>(q),
@@ -884,7 +885,7 @@ rl_status run_forward(rl_decode_ctx* c, const Fwd& f) {
         for (int r0 = 0; r0 < nf; r0 += step) {
             const int nc = std::min(step, nf - r0);
             const uint8_t* hr = static_cast<const uint8_t*>(h) + static_cast<size_t>(r0) * H * esz;
-            GemmArgs a{};
+            GemmArgsX a{};
             a.A = hr; a.lda = H; a.W = c->w.lm_head; a.ldw = H; a.M = nc; a.Nw = V; a.K = H; a.epi = EPI_LSE;
             a.lse = c->wsp<float2>(L.off_part);
             a.T = f.T;
@@ -1181,7 +1182,7 @@ int block_items(const Block& b, int C) {
 }
 
 int choose_chunk(const std::vector<Block>& blocks, int Hkv, int64_t forced, int default_min,
-                 int items_cap, bool decode) {
+                 int items_cap, bool shared) {
     auto count = [&](int C, long* items, long* multi, int* most) {
         *items = 0; *multi = 0; *most = 0;
         for (const Block& b : blocks) {
@@ -1195,29 +1196,18 @@ int choose_chunk(const std::vector<Block>& blocks, int Hkv, int64_t forced, int 
     int most, C;
     if (forced > 0) {
         C = static_cast<int>(forced);
-    } else if (decode) {
-        bool shared = false;
-        for (const Block& b : blocks) shared = shared || (b.src >= 0 && b.plen > 0);
-        if (shared) {
-            // Prompt chunks served from L2 and HBM-bound own parts take very
-            // different times per key: short items let the dispatcher balance
-            // them over the chip.  Over a GRPO rollout, 256 keys per item took
-            // 7.4% less attention time than the long-item rule (512: 6.8% less,
-            // 128: 1% less).
-            C = kSharedDecodeChunk;
-            // few rows: shorter items, so that enough waves stream the keys
-            while (C > 64) {
-                count(C, &items, &multi, &most);
-                if (items * Hkv >= 2 * kAttnWaveTarget) break;
-                C /= 2;
-            }
-        } else {
-            C = 64;
-            while (C < (1 << 16)) {
-                count(2 * C, &items, &multi, &most);
-                if (items * Hkv < kAttnWaveTarget) break;
-                C *= 2;
-            }
+    } else if (shared) {
+        // Prompt chunks served from L2 and HBM-bound own parts take very
+        // different times per key: short items let the dispatcher balance
+        // them over the chip.  Over a GRPO rollout, 256 keys per item took
+        // 7.4% less attention time than the long-item rule (512: 6.8% less,
+        // 128: 1% less).
+        C = kSharedDecodeChunk;
+        // few rows: shorter items, so that enough waves stream the keys
+        while (C > 64) {
+            count(C, &items, &multi, &most);
+            if (items * Hkv >= 2 * kAttnWaveTarget) break;
+            C /= 2;
         }
     } else {
         C = default_min;
@@ -1289,7 +1279,9 @@ std::vector<int> place_shared(const std::vector<AttnItem>& its, const std::vecto
     return order;
 }
 
-rl_status build_items(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks, int C, Fwd* f) {
+// once: every block is the only one of its slot's own keys (decode steps), so
+// each of its items reads keys that no other item of the launch does.
+rl_status build_items(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks, int C, bool once, Fwd* f) {
     std::vector<AttnItem> its;
     std::vector<int64_t> key;
     std::vector<int> split_first;
@@ -1324,6 +1316,7 @@ rl_status build_items(rl_decode_ctx* c, Meta* m, const std::vector<Block>& block
                 it.kv_lo = lo_own + j * C;
                 it.kv_hi = std::min(hi_all, lo_own + (j + 1) * C);
                 key.push_back(-1);
+                it.flags = once ? kAttnOnce : 0;
             }
             it.part = nch > 1 ? part++ : -1;
             it.part0 = part0;
@@ -1412,17 +1405,108 @@ rl_status build_items(rl_decode_ctx* c, Meta* m, const std::vector<Block>& block
             bool same = order[x] >= 0 && key[order[x]] >= 0;
             for (int t = 1; t < 4 && same; ++t) same = order[x + t] >= 0 && key[order[x + t]] == key[order[x]];
             if (same) {
-                items[x].pad = 1;
+                items[x].flags |= kAttnLds;
                 f->plan_lds += 1;
             }
         }
     }
     f->items = dItems;
-    f->n_items = static_cast<int>(order.size());
+    f->wave_first = nullptr;
+    f->n_waves = static_cast<int>(order.size());
     f->n_partial_items = part;
     f->split_blocks = dSplit;
     f->n_split_blocks = static_cast<int>(split_first.size());
     f->attn_score_positions = scorepos;
+    return RL_OK;
+}
+
+// Work items of a decode step that reads no shared prompt: the rows' keys, in
+// 32-position steps one row after the other, are cut into equal runs, one per
+// wave, and every run is one item per row it touches.  All waves then end
+// together whatever the rows' lengths.  A cut within 1 / kCutSnap of a run's
+// length of a row's end moves there (fewer rows to merge).  One wave per SIMD
+// is enough to saturate HBM, since a wave has the next step's loads in flight
+// under each step's math, and more waves only add partials and first loads
+// (101 rows of 600-3400 keys, 7B: 72 us a layer with 1024 waves, 77 with 2048,
+// 82 with 3072; 87 with one item per wave of a power-of-two length and a
+// remainder, where the longest item decided; 48 rows of 1000-6000, 32B: 125 us
+// against 153; 131 rows of 300-1300 on pages, mixture of experts: 47 against 77).
+constexpr int kCutSnap = 16;      // 1 / 16 of a run
+constexpr int kMinRunSteps = 2;   // fewer rows: a run still holds 64 keys
+rl_status build_runs(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks, Fwd* f) {
+    const int Hkv = c->cfg.n_kv_heads;
+    auto steps_of = [](const Block& b) { return ceil_div(b.pos0 + b.nq, 32); };
+    int64_t total = 0;
+    int longest = 0;
+    double scorepos = 0;
+    for (const Block& b : blocks) {
+        total += steps_of(b);
+        longest = std::max(longest, steps_of(b));
+        scorepos += b.pos0 + b.nq;
+    }
+    int64_t waves = std::max(1, kAttnWaveTarget / Hkv);
+    waves = std::min(waves, total / kMinRunSteps);
+    waves = std::min(waves, total * (kMaxCombine - 2) / longest);   // a row is cut into at most kMaxCombine items
+    waves = std::max<int64_t>(waves, 1);
+    const int64_t snap = total / waves / kCutSnap;
+    AttnItem* dItems = nullptr;
+    const size_t cap = blocks.size() + static_cast<size_t>(waves);
+    if (cap > static_cast<size_t>(c->lay.items_cap)) return fail(c, RL_ERR_CAPACITY, "too many attention work items");
+    AttnItem* items = m->take<AttnItem>(cap, &dItems);
+    int32_t *dSplit = nullptr, *dFirst = nullptr;
+    int32_t* split = m->take<int32_t>(blocks.size(), &dSplit);
+    int32_t* first = m->take<int32_t>(static_cast<size_t>(waves) + 1, &dFirst);
+    if (!items || !split || !first) return fail(c, RL_ERR_CAPACITY, "per-call metadata exceeds its workspace region");
+    int n = 0, part = 0, n_split = 0, n_waves = 0;
+    int64_t pos = 0, wave_end = -1;   // steps placed so far, and where the current wave's run ends
+    for (const Block& b : blocks) {
+        const int ns = steps_of(b), hi = b.pos0 + b.nq, n0 = n;
+        const int64_t row_end = pos + ns;
+        int64_t at = pos;
+        while (at < row_end) {
+            if (at >= wave_end) {   // next wave; its run ends at an equal share, or at a row end close to it
+                first[n_waves] = n;
+                ++n_waves;
+                wave_end = std::max(at + 1, total * n_waves / waves);
+                if (n_waves == waves) wave_end = total;
+            }
+            int64_t to = std::min(row_end, wave_end);
+            if (row_end > wave_end && row_end - wave_end <= snap) to = row_end, wave_end = row_end;
+            AttnItem& it = items[n++];
+            std::memset(&it, 0, sizeof(it));
+            it.qrow = b.qrow; it.nq = b.nq; it.slot = b.slot; it.pos0 = b.pos0;
+            it.kv_lo = static_cast<int>(at - pos) * 32;
+            it.kv_hi = std::min<int>(hi, static_cast<int>(to - pos) * 32);
+            it.part = -1; it.qrow_b = -1; it.part_b = -1;
+            it.flags = kAttnOnce;
+            at = to;
+            // a run that ends just past a row's end ends there
+            if (at == row_end && n_waves < waves && wave_end - at <= snap) wave_end = at;
+        }
+        if (n - n0 > 1) {
+            for (int i = n0; i < n; ++i) {
+                items[i].part = part + i - n0;
+                items[i].part0 = part;
+                items[i].nparts = n - n0;
+            }
+            part += n - n0;
+            split[n_split++] = n - 1;
+        } else {
+            items[n0].nparts = 1;
+        }
+        pos = row_end;
+    }
+    first[n_waves] = n;
+    if (part > kPartItems) return fail(c, RL_ERR_CAPACITY, "too many split-KV partials");
+    f->items = dItems;
+    f->wave_first = dFirst;
+    f->n_waves = n_waves;
+    f->n_partial_items = part;
+    f->split_blocks = dSplit;
+    f->n_split_blocks = n_split;
+    f->attn_score_positions = scorepos;
+    f->plan_items = n;
+    f->plan_shared = f->plan_pairs = f->plan_lds = 0;
     return RL_OK;
 }
 
@@ -1458,7 +1542,7 @@ rl_status build_tiles(rl_decode_ctx* c, Meta* m, const std::vector<Block>& block
         for (int t = 0; t < b.nq; ++t) scorepos += b.pos0 + t + 1;
     f->tiles = d;
     f->n_tiles = static_cast<int>(tl.size());
-    f->n_items = 0;
+    f->n_waves = 0;
     f->n_split_blocks = 0;
     f->attn_score_positions = scorepos;
     return RL_OK;
@@ -1743,7 +1827,7 @@ rl_status rl_prefill(rl_decode_ctx* ctx, int32_t n_prompts, int32_t group, const
     f.attn_kv_positions = kvpos;
     if (c->bf16() && c->opt_prefill_items) {
         const int C = choose_chunk(blocks, cf.n_kv_heads, c->opt_chunk, kPrefillChunk, c->lay.items_cap, false);
-        st = build_items(c, &m, blocks, C, &f);
+        st = build_items(c, &m, blocks, C, false, &f);
         if (st != RL_OK) return st;
     } else if (c->bf16()) {
         st = build_tiles(c, &m, blocks, &f);
@@ -1913,7 +1997,7 @@ rl_status rl_score(rl_decode_ctx* ctx, int32_t n_prompts, int32_t group, const i
     f.attn_kv_positions = kvpos;
     if (c->bf16() && c->opt_prefill_items) {
         const int C = choose_chunk(blocks, cf.n_kv_heads, c->opt_chunk, kPrefillChunk, c->lay.items_cap, false);
-        st = build_items(c, &m, blocks, C, &f);
+        st = build_items(c, &m, blocks, C, false, &f);
         if (st != RL_OK) return st;
     } else if (c->bf16()) {
         st = build_tiles(c, &m, blocks, &f);
@@ -2027,8 +2111,14 @@ rl_status rl_decode_step(rl_decode_ctx* ctx, int32_t n, const int32_t* slots, co
     f.attn_kv_positions = kvpos;
     f.attn_score_positions = kvpos;
     if (c->bf16()) {
-        const int C = choose_chunk(blocks, cf.n_kv_heads, c->opt_chunk, 0, c->lay.items_cap, true);
-        st = build_items(c, &m, blocks, C, &f);
+        bool shared = false;
+        for (const Block& b : blocks) shared = shared || (b.src >= 0 && b.plen > 0);
+        if (shared || c->opt_chunk > 0) {
+            const int C = choose_chunk(blocks, cf.n_kv_heads, c->opt_chunk, 0, c->lay.items_cap, shared);
+            st = build_items(c, &m, blocks, C, true, &f);
+        } else {
+            st = build_runs(c, &m, blocks, &f);
+        }
         if (st != RL_OK) return st;
     }
     f.logits = out_logits ? out_logits : c->wsp<float>(c->lay.off_logits);

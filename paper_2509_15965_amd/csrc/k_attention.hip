@@ -27,6 +27,8 @@
 #include "rl_device.h"
 #include "rl_internal.h"
 
+#include <type_traits>
+
 namespace rl {
 
 // Zero the bf16 elements e >= nvalid of an 8-element vector (0 <= nvalid <= 8).
@@ -40,16 +42,29 @@ __device__ __forceinline__ u32x4 mask_tail8(u32x4 v, int nvalid) {
     return v;
 }
 
-// One 32-position step of the online-softmax attention of a wave's 16 query
-// columns: scores of positions t0..t0+31 from the K rows (k0: tile 0, k1:
-// tile 1), positions past min(hi - 1, limit) masked, running max / sum / output
-// updated with the V blocks vf (positions >= hi zeroed).
-template <int D>
-__device__ __forceinline__ void attn_step(const u32x4 (&k0)[D / 32], const u32x4 (&k1)[D / 32],
-                                          const u32x4 (&vf)[D / 16], const u32x4 (&qf)[D / 32], int t0, int hi,
-                                          int limit, int kq, float scale_log2, float& m, float& l,
-                                          f32x4 (&o)[D / 16]) {
-    constexpr int KG = D / 32, DT = D / 16;
+// Two floats as bf16 (round to nearest even) in one word, the first in the low half.
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+
+// Probabilities of one 32-position step for a lane's column, as P.V operands.
+struct StepProbs {
+    u32x4 hi, lo;   // bf16 pair: hi = rne(p), lo = rne(p - hi)
+    float alpha;    // rescale of the running sum and output
+};
+
+// First half of a 32-position step of the online-softmax attention of a wave's
+// 16 query columns: scores of positions t0..t0+31 from the K rows (k0: tile 0,
+// k1: tile 1), positions past min(hi - 1, limit) masked (full: none is, for
+// any lane), running max and sum updated.  after_qk runs once the K registers
+// are consumed, so that the caller can refill them under the softmax.
+template <int D, typename AfterQk>
+__device__ __forceinline__ StepProbs attn_scores(const u32x4 (&k0)[D / 32], const u32x4 (&k1)[D / 32],
+                                                 const u32x4 (&qf)[D / 32], int t0, int hi, int limit, bool full,
+                                                 int kq, float scale_log2, float& m, float& l, AfterQk after_qk) {
+    constexpr int KG = D / 32;
     const int pb = t0 + 8 * kq;
     f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -57,13 +72,19 @@ __device__ __forceinline__ void attn_step(const u32x4 (&k0)[D / 32], const u32x4
         s0 = mfma16x16x32(as_bf16x8(k0[j]), as_bf16x8(qf[j]), s0);
         s1 = mfma16x16x32(as_bf16x8(k1[j]), as_bf16x8(qf[j]), s1);
     }
+    after_qk();
     // this lane now holds the scores of its column at positions pb + 0..7
-    const int lim = min(hi - 1, limit);
     float sv[8];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        sv[e] = (pb + e <= lim) ? s0[e] * scale_log2 : -INFINITY;
-        sv[4 + e] = (pb + 4 + e <= lim) ? s1[e] * scale_log2 : -INFINITY;
+        sv[e] = s0[e] * scale_log2;
+        sv[4 + e] = s1[e] * scale_log2;
+    }
+    if (!full) {
+        const int lim = min(hi - 1, limit);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (pb + e > lim) sv[e] = -INFINITY;
     }
     float mx = sv[0];
 #pragma unroll
@@ -72,34 +93,49 @@ __device__ __forceinline__ void attn_step(const u32x4 (&k0)[D / 32], const u32x4
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
     const float m_new = fmaxf(m, mx);
     const float m_use = m_new == -INFINITY ? 0.0f : m_new;
-    const float alpha = exp2f(m - m_use);
-    // probabilities as a bf16 pair hi + lo (hi = rne(p), lo = rne(p - hi)):
-    // the P.V product then carries ~16 significant bits of p, so the only
+    StepProbs r;
+    r.alpha = __builtin_amdgcn_exp2f(m - m_use);
+    // the P.V product carries ~16 significant bits of p (hi + lo), so the only
     // storage rounding left is the one of the attention output
     float psum = 0.0f;
-    uint32_t ph[4], pl[4];
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        const float p0 = exp2f(sv[2 * w] - m_use);
-        const float p1 = exp2f(sv[2 * w + 1] - m_use);
+        const float p0 = __builtin_amdgcn_exp2f(sv[2 * w] - m_use);
+        const float p1 = __builtin_amdgcn_exp2f(sv[2 * w + 1] - m_use);
         psum += p0 + p1;
-        const uint16_t h0 = f32_to_bf16(p0), h1 = f32_to_bf16(p1);
-        const uint16_t l0 = f32_to_bf16(p0 - bf16_to_f32(h0)), l1 = f32_to_bf16(p1 - bf16_to_f32(h1));
-        ph[w] = static_cast<uint32_t>(h0) | (static_cast<uint32_t>(h1) << 16);
-        pl[w] = static_cast<uint32_t>(l0) | (static_cast<uint32_t>(l1) << 16);
+        const uint32_t h = pack_bf16(p0, p1);
+        r.hi[w] = h;
+        r.lo[w] = pack_bf16(p0 - __uint_as_float(h << 16), p1 - __uint_as_float(h & 0xFFFF0000u));
     }
-    l = l * alpha + psum;
+    l = l * r.alpha + psum;
     m = m_new;
-    const u32x4 pfh = {ph[0], ph[1], ph[2], ph[3]};
-    const u32x4 pfl = {pl[0], pl[1], pl[2], pl[3]};
-    const int nvalid = hi - pb;   // keys past the chunk end carry no data
+    return r;
+}
+
+// Second half: the output rescaled and updated with the V blocks vf
+// (positions >= hi zeroed unless full).
+template <int D>
+__device__ __forceinline__ void attn_pv(const u32x4 (&vf)[D / 16], const StepProbs& p, int t0, int hi, bool full,
+                                        int kq, f32x4 (&o)[D / 16]) {
+    constexpr int DT = D / 16;
+    const int nvalid = hi - (t0 + 8 * kq);   // keys past the chunk end carry no data
 #pragma unroll
     for (int i = 0; i < DT; ++i) {
-        u32x4 v = nvalid < 8 ? mask_tail8(vf[i], nvalid < 0 ? 0 : nvalid) : vf[i];
-        o[i] = o[i] * alpha;
-        o[i] = mfma16x16x32(as_bf16x8(v), as_bf16x8(pfh), o[i]);
-        o[i] = mfma16x16x32(as_bf16x8(v), as_bf16x8(pfl), o[i]);
+        u32x4 v = vf[i];
+        if (!full && nvalid < 8) v = mask_tail8(v, nvalid < 0 ? 0 : nvalid);
+        o[i] = o[i] * p.alpha;
+        o[i] = mfma16x16x32(as_bf16x8(v), as_bf16x8(p.hi), o[i]);
+        o[i] = mfma16x16x32(as_bf16x8(v), as_bf16x8(p.lo), o[i]);
     }
+}
+
+template <int D>
+__device__ __forceinline__ void attn_step(const u32x4 (&k0)[D / 32], const u32x4 (&k1)[D / 32],
+                                          const u32x4 (&vf)[D / 16], const u32x4 (&qf)[D / 32], int t0, int hi,
+                                          int limit, bool full, int kq, float scale_log2, float& m, float& l,
+                                          f32x4 (&o)[D / 16]) {
+    const StepProbs p = attn_scores<D>(k0, k1, qf, t0, hi, limit, full, kq, scale_log2, m, l, [] {});
+    attn_pv<D>(vf, p, t0, hi, full, kq, o);
 }
 
 // 16-byte chunk permutation of K row r (of a 32-position step) in LDS:
@@ -159,167 +195,183 @@ __device__ __forceinline__ void wait_vm0() { __builtin_amdgcn_s_waitcnt((7 << 4)
 // looks its page up; otherwise the slot's block is fixed for the item.
 template <int D, bool PAGED>
 __global__ void __launch_bounds__(256, 2) attn_bf16_kernel(const AttnItem* __restrict__ items,
-        int n_items, const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc,
-        const uint16_t* __restrict__ vc, KvPages kp, int Hq, int Hkv, int layer,
+        const int32_t* __restrict__ wave_first, int n_waves, const uint16_t* __restrict__ q,
+        const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc, KvPages kp, int Hq, int Hkv, int layer,
         float scale_log2, uint16_t* __restrict__ out, float* __restrict__ part) {
     constexpr int KG = D / 32;   // 32-wide k groups of a head
     constexpr int DT = D / 16;   // 16-wide d tiles of the output
     constexpr int STEPB = 32 * D * 2;
     __shared__ __attribute__((aligned(1024))) uint8_t lds[2][2][STEPB];   // [buffer][K | V], shared-chunk units
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int item_id = blockIdx.x * 4 + wave;
-    // a unit of four items over one shared prompt chunk (same slot and key
-    // range; the host sets pad = 1 on its first item): every K/V step goes
-    // through LDS once for the four waves
-    const bool wg_lds = blockIdx.x * 4 + 3 < n_items && items[blockIdx.x * 4].pad == 1;
-    if (item_id >= n_items) return;
+    // the wave index as a scalar: the item, its addresses and its page table
+    // reads then are scalar too
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wid = blockIdx.x * 4 + wave;
+    if (wid >= n_waves) return;
     const int kvh = blockIdx.y;
     const int G = Hq / Hkv;
-    const AttnItem it = items[item_id];
+    // the wave's items: consecutive ones up to the next wave's first, or the
+    // wave's own number without a list
+    const int first = wave_first ? wave_first[wid] : wid, last = wave_first ? wave_first[wid + 1] : wid + 1;
+    // a unit of four items over one shared prompt chunk (same slot and key
+    // range; the host flags its first item): every K/V step goes through LDS
+    // once for the four waves
+    const bool wg_lds = !wave_first && blockIdx.x * 4 + 3 < n_waves && (items[blockIdx.x * 4].flags & kAttnLds) != 0;
+    for (int item_id = first; item_id < last; ++item_id) {
+        const AttnItem it = items[item_id];
 
-    const int col = lane & 15, kq = lane >> 4;
-    const int ncols = it.nq * G;
-    const bool cvalid = col < ncols;
-    const int tau = cvalid ? col / G : 0;
-    const int head = kvh * G + (cvalid ? col - tau * G : 0);
-    const bool second = it.qrow_b >= 0 && tau == 1;   // second sequence of a pair item
-    const int qrow = second ? it.qrow_b : it.qrow + tau;
-    const int limit = cvalid ? it.pos0 + tau : -1;   // last key this column sees
+        const int col = lane & 15, kq = lane >> 4;
+        const int ncols = it.nq * G;
+        const bool cvalid = col < ncols;
+        const int tau = cvalid ? col / G : 0;
+        const int head = kvh * G + (cvalid ? col - tau * G : 0);
+        const bool second = it.qrow_b >= 0 && tau == 1;   // second sequence of a pair item
+        const int qrow = second ? it.qrow_b : it.qrow + tau;
+        const int limit = cvalid ? it.pos0 + tau : -1;   // last key this column sees
 
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-    u32x4 qf[KG];
-    {
-        const uint16_t* qp = q + (static_cast<size_t>(qrow) * Hq + head) * D + 8 * kq;
+        const u32x4 zero = {0u, 0u, 0u, 0u};
+        u32x4 qf[KG];
+        {
+            const uint16_t* qp = q + (static_cast<size_t>(qrow) * Hq + head) * D + 8 * kq;
 #pragma unroll
-        for (int j = 0; j < KG; ++j) qf[j] = cvalid ? ld16(qp + 32 * j) : zero;
-    }
+            for (int j = 0; j < KG; ++j) qf[j] = cvalid ? ld16(qp + 32 * j) : zero;
+        }
 
-    // K / V block of the step at position t0 (element pointers) and t0's
-    // position inside it.  A paged item reads the table entry of its first
-    // page here, right after the q loads, and each later entry one page
-    // ahead (steps ascend 32 positions at a time, so they enter pages in
-    // order).
-    size_t base = 0;
-    int base_page = 0, next_pid = 0;
-    if (!PAGED) {
-        base = kv_block(kp, layer, Hkv, it.slot, kvh);
-    } else {
-        base_page = it.kv_lo / kp.page;
-        if (base_page < kp.maxp) base = kv_block(kp, layer, Hkv, kv_clamp(kp, kv_table(kp, it.slot, base_page)), kvh);
-        if (base_page + 1 < kp.maxp) next_pid = kv_table(kp, it.slot, base_page + 1);
-    }
-    auto block_of = [&](int t0, const uint16_t** kbp, const uint16_t** vbp) {
-        int lt = t0;
-        if (PAGED) {
-            const int j = t0 / kp.page;
-            if (j != base_page) {
-                const int pid = j == base_page + 1 ? next_pid : kv_table(kp, it.slot, j);
-                base = kv_block(kp, layer, Hkv, kv_clamp(kp, pid), kvh);
-                base_page = j;
-                next_pid = j + 1 < kp.maxp ? kv_table(kp, it.slot, j + 1) : 0;
+        // The K / V block of the current step and the step's position inside it.
+        // Steps ascend 32 positions at a time and pages are multiples of 32, so a
+        // paged item enters its pages in order; each table entry is read one page
+        // ahead.
+        size_t base = 0;
+        int lt = it.kv_lo, page_j = 0, next_pid = 0;
+        if (!PAGED) {
+            base = kv_block(kp, layer, Hkv, it.slot, kvh);
+        } else {
+            page_j = it.kv_lo / kp.page;
+            lt = it.kv_lo - page_j * kp.page;
+            if (page_j < kp.maxp) base = kv_block(kp, layer, Hkv, kv_clamp(kp, kv_table(kp, it.slot, page_j)), kvh);
+            if (page_j + 1 < kp.maxp) next_pid = kv_table(kp, it.slot, page_j + 1);
+        }
+        auto advance = [&] {
+            lt += 32;
+            if (PAGED && lt == kp.page) {
+                lt = 0;
+                ++page_j;
+                base = kv_block(kp, layer, Hkv, kv_clamp(kp, next_pid), kvh);
+                next_pid = page_j + 1 < kp.maxp ? kv_table(kp, it.slot, page_j + 1) : 0;
             }
-            lt = t0 - j * kp.page;
-        }
-        *kbp = kc + base;
-        *vbp = vc + base;
-        return lt;
-    };
+        };
 
-    float m = -INFINITY, l = 0.0f;
-    f32x4 o[DT];
+        float m = -INFINITY, l = 0.0f;
+        f32x4 o[DT];
 #pragma unroll
-    for (int i = 0; i < DT; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < DT; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    const int hi = it.kv_hi;
-    // key row r of score tile 0 is position t0 + 8(r/4) + r%4; tile 1 adds 4
-    const int krow = 8 * (col >> 2) + (col & 3);
-    // K rows and V blocks of one 32-position step, loaded and then used (the
-    // waves resident on the chip keep HBM busy without a per-wave prefetch)
-    u32x4 k0[KG], k1[KG], vf[DT];
-    auto load_step = [&](int t0, u32x4 (&a0)[KG], u32x4 (&a1)[KG], u32x4 (&vv)[DT]) {
-        const uint16_t *kb, *vb;
-        const int lt = block_of(t0, &kb, &vb);
-        const uint16_t* kp0 = kb + static_cast<size_t>(lt + krow) * D + 8 * kq;
-        const uint16_t* kp1 = kp0 + 4 * D;
+        const int hi = it.kv_hi;
+        // a step before this position masks no key of any valid column (columns
+        // without a query are never stored)
+        const int full_end = min(hi, it.pos0 + 1);
+        // key row r of score tile 0 is position t0 + 8(r/4) + r%4; tile 1 adds 4
+        const int krow = 8 * (col >> 2) + (col & 3);
+        const uint32_t koff = krow * D + 8 * kq, voff = (kq * D + col) * 8;   // this lane's element in a step
+        u32x4 k0[KG], k1[KG], vf[DT];
+        if (wg_lds) {
+            const int nsteps = (hi - it.kv_lo + 31) / 32;
+            if (nsteps > 0) step_dma<D, 4>(kc + base, vc + base, lt, wave, lane, lds[0][0], lds[0][1]);
+            for (int s = 0; s < nsteps; ++s) {
+                wait_vm0();        // this wave's DMAs (and q loads) landed
+                __syncthreads();   // every wave's part of step s is in LDS; step s-1 retired
+                if (s + 1 < nsteps) {
+                    advance();
+                    step_dma<D, 4>(kc + base, vc + base, lt, wave, lane, lds[(s + 1) & 1][0], lds[(s + 1) & 1][1]);
+                }
+                const int t0 = it.kv_lo + 32 * s;
+                step_frags<D>(lds[s & 1][0], lds[s & 1][1], krow, kq, col, k0, k1, vf);
+                attn_step<D>(k0, k1, vf, qf, t0, hi, limit, t0 + 32 <= full_end, kq, scale_log2, m, l, o);
+            }
+        } else if (hi > it.kv_lo) {
+            // K and V registers are refilled for the next step as soon as this
+            // one has consumed them, so a wave always has loads in flight under
+            // its math, in the same registers.  Keys that this item alone reads
+            // carry the non-temporal hint: streaming them through the memory-side
+            // cache evicts the activations and partial sums written there, which
+            // then cross HBM twice.
+            auto run = [&](auto once) {
+                constexpr bool NT = decltype(once)::value;
+                auto ld = [](const uint16_t* q_) { return NT ? ld16_nt(q_) : ld16(q_); };
+                auto load_k = [&] {
+                    const uint16_t* kb = kc + base + static_cast<size_t>(lt) * D;
 #pragma unroll
-        for (int j = 0; j < KG; ++j) {
-            a0[j] = ld16(kp0 + 32 * j);
-            a1[j] = ld16(kp1 + 32 * j);
-        }
-        const uint16_t* vp = vb + (static_cast<size_t>((lt + 8 * kq) >> 3) * D + col) * 8;
+                    for (int j = 0; j < KG; ++j) {
+                        k0[j] = ld(kb + koff + 32 * j);
+                        k1[j] = ld(kb + koff + 4 * D + 32 * j);
+                    }
+                };
+                auto load_v = [&] {
+                    const uint16_t* vb = vc + base + static_cast<size_t>(lt) * D;
 #pragma unroll
-        for (int i = 0; i < DT; ++i) vv[i] = ld16(vp + 16 * 8 * i);
-    };
-    auto dma_step = [&](int t0, int buf) {
-        const uint16_t *kb, *vb;
-        const int lt = block_of(t0, &kb, &vb);
-        step_dma<D, 4>(kb, vb, lt, wave, lane, lds[buf][0], lds[buf][1]);
-    };
-    if (wg_lds) {
-        const int nsteps = (hi - it.kv_lo + 31) / 32;
-        if (nsteps > 0) dma_step(it.kv_lo, 0);
-        for (int s = 0; s < nsteps; ++s) {
-            wait_vm0();        // this wave's DMAs (and q loads) landed
-            __syncthreads();   // every wave's part of step s is in LDS; step s-1 retired
-            if (s + 1 < nsteps) dma_step(it.kv_lo + 32 * (s + 1), (s + 1) & 1);
-            step_frags<D>(lds[s & 1][0], lds[s & 1][1], krow, kq, col, k0, k1, vf);
-            attn_step<D>(k0, k1, vf, qf, it.kv_lo + 32 * s, hi, limit, kq, scale_log2, m, l, o);
+                    for (int i = 0; i < DT; ++i) vf[i] = ld(vb + voff + 128 * i);
+                };
+                load_k();
+                load_v();
+                for (int t0 = it.kv_lo; t0 < hi; t0 += 32) {
+                    const bool more = t0 + 32 < hi, full = t0 + 32 <= full_end;
+                    const StepProbs p = attn_scores<D>(k0, k1, qf, t0, hi, limit, full, kq, scale_log2, m, l, [&] {
+                        if (more) {
+                            advance();
+                            load_k();
+                        }
+                    });
+                    attn_pv<D>(vf, p, t0, hi, full, kq, o);
+                    if (more) load_v();
+                }
+            };
+            if (it.flags & kAttnOnce) run(std::true_type{});
+            else run(std::false_type{});
         }
-    } else {
-        for (int t0 = it.kv_lo; t0 < hi; t0 += 32) {
-            load_step(t0, k0, k1, vf);
-            attn_step<D>(k0, k1, vf, qf, t0, hi, limit, kq, scale_log2, m, l, o);
-        }
-    }
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
+        l += __shfl_xor(l, 16, 64);
+        l += __shfl_xor(l, 32, 64);
 
-    // lane holds O^T[d = 16 i + 4 kq + e][col]
-    if (it.part < 0) {
-        if (!cvalid) return;
-        const float inv = 1.0f / l;
-        uint16_t* op = out + (static_cast<size_t>(qrow) * Hq + head) * D + 4 * kq;
+        // lane holds O^T[d = 16 i + 4 kq + e][col]
+        if (it.part < 0) {
+            if (!cvalid) continue;
+            const float inv = 1.0f / l;
+            uint16_t* op = out + (static_cast<size_t>(qrow) * Hq + head) * D + 4 * kq;
 #pragma unroll
-        for (int i = 0; i < DT; ++i) {
-            const uint32_t w0 = static_cast<uint32_t>(f32_to_bf16(o[i][0] * inv)) |
-                                (static_cast<uint32_t>(f32_to_bf16(o[i][1] * inv)) << 16);
-            const uint32_t w1 = static_cast<uint32_t>(f32_to_bf16(o[i][2] * inv)) |
-                                (static_cast<uint32_t>(f32_to_bf16(o[i][3] * inv)) << 16);
-            *reinterpret_cast<uint2*>(op + 16 * i) = make_uint2(w0, w1);
+            for (int i = 0; i < DT; ++i) {
+                const uint32_t w0 = static_cast<uint32_t>(f32_to_bf16(o[i][0] * inv)) |
+                                    (static_cast<uint32_t>(f32_to_bf16(o[i][1] * inv)) << 16);
+                const uint32_t w1 = static_cast<uint32_t>(f32_to_bf16(o[i][2] * inv)) |
+                                    (static_cast<uint32_t>(f32_to_bf16(o[i][3] * inv)) << 16);
+                *reinterpret_cast<uint2*>(op + 16 * i) = make_uint2(w0, w1);
+            }
+            continue;
         }
-        return;
-    }
-    // split block: (m, l, unnormalised o) partials, merged by attn_combine
-    if (!cvalid) return;
-    // a pair item's second sequence owns its own partial slot (columns from 0)
-    const int pidx = second ? it.part_b : it.part;
-    const int pcol = second ? col - G : col;
-    float* pp = part + ((static_cast<size_t>(pidx) * Hkv + kvh) * 16 + pcol) * (D + 2);
+        // split block: (unnormalised o, then m and l) partials, merged by attn_combine
+        if (!cvalid) continue;
+        // a pair item's second sequence owns its own partial slot (columns from 0)
+        const int pidx = second ? it.part_b : it.part;
+        const int pcol = second ? col - G : col;
+        float* pb = part + (static_cast<size_t>(pidx) * Hkv + kvh) * 16 * (D + 2);
 #pragma unroll
-    for (int i = 0; i < DT; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) pp[16 * i + 4 * kq + e] = o[i][e];
-    if (kq == 0) {
-        pp[D] = m;
-        pp[D + 1] = l;
+        for (int i = 0; i < DT; ++i) *reinterpret_cast<f32x4*>(pb + pcol * D + 16 * i + 4 * kq) = o[i];
+        if (kq == 0) *reinterpret_cast<float2*>(pb + 16 * D + 2 * pcol) = make_float2(m, l);
     }
 }
 
-hipError_t launch_attention_bf16(const AttnItem* items, int n_items, const void* q,
+hipError_t launch_attention_bf16(const AttnItem* items, const int32_t* wave_first, int n_waves, const void* q,
                                  const void* kc, const void* vc, const KvPages& kp, int Hq, int Hkv,
                                  int D, int layer, void* out, float* part,
                                  hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
-    if (n_items <= 0) return hipSuccess;
+    if (n_waves <= 0) return hipSuccess;
     const float scale_log2 = 1.4426950408889634f / sqrtf(static_cast<float>(D));
-    dim3 grid((n_items + 3) / 4, Hkv), block(256);
+    dim3 grid((n_waves + 3) / 4, Hkv), block(256);
     auto go = [&](auto kern) {
         if (ev_start || ev_stop)
-            hipExtLaunchKernelGGL(kern, grid, block, 0, s, ev_start, ev_stop, 0, items, n_items,
+            hipExtLaunchKernelGGL(kern, grid, block, 0, s, ev_start, ev_stop, 0, items, wave_first, n_waves,
                                   static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(kc),
                                   static_cast<const uint16_t*>(vc), kp, Hq, Hkv, layer, scale_log2,
                                   static_cast<uint16_t*>(out), part);
         else
-            hipLaunchKernelGGL(kern, grid, block, 0, s, items, n_items, static_cast<const uint16_t*>(q),
+            hipLaunchKernelGGL(kern, grid, block, 0, s, items, wave_first, n_waves, static_cast<const uint16_t*>(q),
                                static_cast<const uint16_t*>(kc), static_cast<const uint16_t*>(vc), kp, Hq,
                                Hkv, layer, scale_log2, static_cast<uint16_t*>(out), part);
     };
@@ -398,7 +450,7 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) attn_prefill_kernel(const 
         if (nq == 0 || t0 > wave_last) continue;       // wave-uniform: nothing of this step is visible
         u32x4 k0[KG], k1[KG], vf[DT];
         step_frags<D>(lds[s & 1][0], lds[s & 1][1], krow, kq, col, k0, k1, vf);
-        attn_step<D>(k0, k1, vf, qf, t0, hi, limit, kq, scale_log2, m, l, o);
+        attn_step<D>(k0, k1, vf, qf, t0, hi, limit, t0 + 32 <= tl.pos0 + tok0 + 1, kq, scale_log2, m, l, o);
     }
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
@@ -432,63 +484,63 @@ hipError_t launch_attention_prefill(const PrefillTile* tiles, int n_tiles, const
     return hipGetLastError();
 }
 
-// Merge the split partials of one query block and q-head: one workgroup per
-// (split block, q-head), one thread per d, the block's tokens in turn.  Lane
-// j of each wave loads item j's (m, l) (at most 64 items), the token's max
-// comes from a wave reduction, and each thread sums its own column of the
-// partial outputs in item order, 8 loads in flight at a time, reading the
-// items' (m, l) from their lanes.  Weights 2^(m_j - M).
+// Merge the split partials of one query block and kv-head: one workgroup per
+// (split block, kv-head), one thread per four output dimensions of a q-head,
+// the block's tokens in turn.  Partials are taken eight at a time, in item
+// order, with every load of the eight in flight at once; weights 2^(m_j - M).
+// Latency bound (two round trips up to eight partials).
 template <int D>
-__global__ void __launch_bounds__(D) attn_combine_kernel(const int32_t* __restrict__ blocks,
+__global__ void __launch_bounds__(16 * D / 4) attn_combine_kernel(const int32_t* __restrict__ blocks,
         const AttnItem* __restrict__ items, const float* __restrict__ part, int Hq, int Hkv,
         uint16_t* __restrict__ out) {
-    static_assert(kMaxCombine <= 64, "one item per lane");
     const AttnItem it = items[blocks[blockIdx.x]];
-    const int h = blockIdx.y;
-    const int G = Hq / Hkv;
-    const int kvh = h / G, g = h - kvh * G;
+    const int kvh = blockIdx.y, G = Hq / Hkv;
+    const int g = threadIdx.x / (D / 4), d4 = threadIdx.x % (D / 4);
+    if (g >= G) return;
     const int np = it.nparts;
-    const int d = threadIdx.x, lane = threadIdx.x & 63;
     const size_t pstride = static_cast<size_t>(Hkv) * 16 * (D + 2);
-    const float* pb0 = part + (static_cast<size_t>(it.part0) * Hkv + kvh) * 16 * (D + 2);
-    auto lane_f = [](float v, int src) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));
-    };
+    const float* pb = part + (static_cast<size_t>(it.part0) * Hkv + kvh) * 16 * (D + 2);
     for (int t = 0; t < it.nq; ++t) {
-        const float* pc = pb0 + static_cast<size_t>(t * G + g) * (D + 2);
-        const float mv = lane < np ? pc[lane * pstride + D] : -INFINITY;
-        const float lv = lane < np ? pc[lane * pstride + D + 1] : 0.0f;
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (u < np) v[u] = pc[u * pstride + d];
-        float M = mv;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
-        float acc = 0.0f, L = 0.0f;
+        const int c = t * G + g;
+        const float* po = pb + c * D + 4 * d4;
+        const float* pm = pb + 16 * D + 2 * c;
+        float M = -INFINITY, L = 0.0f;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
         for (int j = 0; j < np; j += 8) {
-            if (j > 0) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (j + u < np) v[u] = pc[(j + u) * pstride + d];
-            }
+            float2 ml[8];
+            f32x4 v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                if (j + u < np) {
-                    const float w = exp2f(lane_f(mv, j + u) - M);
-                    L += w * lane_f(lv, j + u);
-                    acc += w * v[u];
-                }
+                const bool in = j + u < np;
+                ml[u] = in ? *reinterpret_cast<const float2*>(pm + (j + u) * pstride) : make_float2(-INFINITY, 0.f);
+                v[u] = in ? *reinterpret_cast<const f32x4*>(po + (j + u) * pstride) : f32x4{0.f, 0.f, 0.f, 0.f};
             }
+            float Mn = M;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) Mn = fmaxf(Mn, ml[u].x);
+            const float Mu = Mn == -INFINITY ? 0.0f : Mn;
+            const float al = exp2f(M - Mu);
+            L *= al;
+            acc = acc * al;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float w = exp2f(ml[u].x - Mu);
+                L += w * ml[u].y;
+                acc += v[u] * w;
+            }
+            M = Mn;
         }
-        out[(static_cast<size_t>(it.qrow + t) * Hq + h) * D + d] = f32_to_bf16(acc / L);
+        const float inv = 1.0f / L;
+        *reinterpret_cast<uint2*>(out + (static_cast<size_t>(it.qrow + t) * Hq + kvh * G + g) * D + 4 * d4) =
+            make_uint2(pack_bf16(acc[0] * inv, acc[1] * inv), pack_bf16(acc[2] * inv, acc[3] * inv));
     }
 }
 
 hipError_t launch_attn_combine(const int32_t* blocks, int n_blocks, const AttnItem* items, const float* part,
                                int Hq, int Hkv, int D, void* out, hipStream_t s) {
     if (n_blocks <= 0) return hipSuccess;
-    dim3 grid(n_blocks, Hq), block(D);
+    const int threads = (Hq / Hkv * (D / 4) + 63) / 64 * 64;
+    dim3 grid(n_blocks, Hkv), block(threads);
     if (D == 128)
         hipLaunchKernelGGL(attn_combine_kernel<128>, grid, block, 0, s, blocks, items, part, Hq, Hkv,
                            static_cast<uint16_t*>(out));

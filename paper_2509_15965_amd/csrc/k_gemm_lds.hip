@@ -200,8 +200,10 @@ __device__ __forceinline__ void dma16(const uint16_t* g, uint8_t* lds_wave_base)
 // Same, from a wave-uniform base plus a 32-bit per-lane byte offset: the
 // address then stays in the scalar-base form of the instruction (no 64-bit
 // per-lane address arithmetic per issue).
+constexpr int kNonTemporal = 2;   // cache policy bits of the load instructions: NT
+template <int CPOL = 0>
 __device__ __forceinline__ void dma16_off(const uint8_t* base, uint32_t off, uint8_t* lds_wave_base) {
-    __builtin_amdgcn_global_load_lds(static_cast<const void*>(base + off), (lds_void_t*)(lds_wave_base), 16, 0, 0);
+    __builtin_amdgcn_global_load_lds(static_cast<const void*>(base + off), (lds_void_t*)(lds_wave_base), 16, 0, CPOL);
 }
 
 // s_waitcnt vmcnt(n) with the other counters left alone (gfx9 encoding)
@@ -448,8 +450,14 @@ struct TileMap {
 // MODE 0: whole tiles with the epilogue; 1: split-K, partial tiles [split][M][Nw];
 // 2: whole tiles with the epilogue and a K-cut remainder (TileMap::rem); 3: the
 // experts' row tiles of a mixture of experts (GemmArgs::g_*)
-template <int BM, int BN, int WM, int NW, int SA, int SW, int EPI, int MODE>
-__global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ksplit, TileMap tm, int n0) {
+// WNT: weight loads carry the non-temporal hint.  Where a weight tile is read by
+// one workgroup only (a single row tile), keeping it in the caches evicts the
+// written activations and partial sums there, which then travel to HBM and
+// back; with several row tiles the hint costs 3% (8192 rows: 1064 -> 1031
+// TFLOP/s) because they share the tile in L2.
+template <int BM, int BN, int WM, int NW, int SA, int SW, int EPI, int MODE, bool WNT>
+__global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(
+        std::conditional_t<MODE == 3 || EPI == EPI_LSE, GemmArgsX, GemmArgs> p, int ksplit, TileMap tm, int n0) {
     constexpr int BK = 64, ROWB = 128;
     constexpr int WN = NW / WM;
     constexpr int TM = BM / WM, TN = BN / WN;
@@ -461,6 +469,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
     static_assert(SA >= 2 && SW >= 2 && SA <= 6 && SW <= 6, "ring depths");
     constexpr int SMAX = SA > SW ? SA : SW;   // the prologue covers iterations -SMAX .. -1
     static_assert(SA * AQ + SW * BQ < 64, "vmcnt range (most loads ever in flight)");
+    constexpr int WCP = WNT ? kNonTemporal : 0;
     __shared__ __attribute__((aligned(1024))) uint8_t smem[SA * ASTAGE + SW * BSTAGE];
 
     const int w = blockIdx.x;
@@ -469,7 +478,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
     int cut = -1;   // MODE 2: partial tile written by a remainder workgroup
     int row0 = 0, M = p.M;   // MODE 3: the expert's pair positions [row0, M)
     const uint16_t* W = static_cast<const uint16_t*>(p.W);
-    if (MODE == 3) {
+    if constexpr (MODE == 3) {
         // an expert's tiles are consecutive, row tiles fastest, so the row
         // tiles that share a weight tile run together; tiles are counted on
         // the device and shared out equally over the XCDs
@@ -548,7 +557,8 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
         const int g = wave * AQ + q;
         int m = m0 + 8 * g + lrow;
         m = m < M ? m : M - 1;
-        if (MODE == 3 && EPI == EPI_SWIGLU) m = min(max(p.g_pairs[m], 0), p.g_npairs - 1) / p.g_k;   // the pair's token row
+        if constexpr (MODE == 3 && EPI == EPI_SWIGLU)   // the pair's token row
+            m = min(max(p.g_pairs[m], 0), p.g_npairs - 1) / p.g_k;
         const int ch = (lane & 7) ^ (((8 * g + lrow) >> 1) & 7);
         aoff[q] = 2u * (static_cast<uint32_t>(m) * static_cast<uint32_t>(p.lda) + 8u * ch);
     }
@@ -564,11 +574,13 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
     // MODE 3, down: the plane row and routing weight of the tile's row tid
     int prow = 0;
     float pwt = 0.0f;
-    if (MODE == 3 && EPI == EPI_RESID && tid < BM && m0 + tid < M) {
-        const int pr = min(max(p.g_pairs[m0 + tid], 0), p.g_npairs - 1);
-        const int row = pr / p.g_k;
-        prow = (pr - row * p.g_k) * p.g_rows + row;
-        pwt = p.g_pw[pr];
+    if constexpr (MODE == 3 && EPI == EPI_RESID) {
+        if (tid < BM && m0 + tid < M) {
+            const int pr = min(max(p.g_pairs[m0 + tid], 0), p.g_npairs - 1);
+            const int row = pr / p.g_k;
+            prow = (pr - row * p.g_k) * p.g_rows + row;
+            pwt = p.g_pw[pr];
+        }
     }
     uint8_t* const abuf = smem;
     uint8_t* const bbuf = smem + SA * ASTAGE;
@@ -582,7 +594,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
         uint8_t* base = bbuf + (stage % SW) * BSTAGE;
         const uint8_t* src = reinterpret_cast<const uint8_t*>(W + kb + stage * BK);
 #pragma unroll
-        for (int q = 0; q < BQ; ++q) dma16_off(src, boff[q], base + (wave * BQ + q) * 1024);
+        for (int q = 0; q < BQ; ++q) dma16_off<WCP>(src, boff[q], base + (wave * BQ + q) * 1024);
     };
     // Issue schedule: in (real or prologue) iteration i, A(i + SA) if in range,
     // then W(i + SW) if in range; the prologue is iterations -SMAX .. -1.
@@ -656,7 +668,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(GemmArgs p, int ks
 #pragma unroll
             for (int d = (ND * g) / NMF; d < (ND * (g + 1)) / NMF; ++d) {
                 if (d < AQ) dma16_off(srca, aoff[d], ldsa + d * 1024);
-                else dma16_off(srcw, boff[d - AQ], ldsw + (d - AQ) * 1024);
+                else dma16_off<WCP>(srcw, boff[d - AQ], ldsw + (d - AQ) * 1024);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -931,8 +943,15 @@ hipError_t launch_dma128(const GemmArgs& a, const GemmPlan& p, int n0, int n1, h
     tm.xsplit = p.splits >= 8 && p.splits % 8 == 0;
     const dim3 block(64 * NW);
     const dim3 grid = tm.xsplit ? dim3(8 * tm.whole, p.splits / 8) : dim3((tm.whole + 7) / 8 * 8, p.splits);
-#define RL_DMA(EPI, MODE) \
-    hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, WM, NW, SA, SW, EPI, MODE>), grid, block, 0, s, a, p.ksplit, tm, n0)
+#define RL_DMA(EPI, MODE)                                                                                              \
+    do {                                                                                                              \
+        if (tm.m_tiles == 1)                                                                                          \
+            hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, WM, NW, SA, SW, EPI, MODE, true>), grid, block, 0, s, a,    \
+                               p.ksplit, tm, n0);                                                                     \
+        else                                                                                                          \
+            hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, WM, NW, SA, SW, EPI, MODE, false>), grid, block, 0, s, a,   \
+                               p.ksplit, tm, n0);                                                                     \
+    } while (0)
     if (p.splits > 1) {
         if (a.epi == EPI_SWIGLU) RL_DMA(EPI_SWIGLU, 1);
         else RL_DMA(EPI_F32, 1);
@@ -973,7 +992,7 @@ hipError_t launch_cut256(const GemmArgs& a, hipStream_t s) {
     const dim3 grid((tm.whole + 7) / 8 * 8 + tm.rem * tm.rem_splits), block(64 * NW), fgrid(tm.rem, BM / 16);
 #define RL_CUT(EPI)                                                                                                   \
     do {                                                                                                              \
-        hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, WM, NW, 2, 3, EPI, 2>), grid, block, 0, s, a, a.K, tm, 0);      \
+        hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, WM, NW, 2, 3, EPI, 2, false>), grid, block, 0, s, a, a.K, tm, 0);      \
         hipLaunchKernelGGL((finish_tiles_kernel<BM, BN, TN, EPI>), fgrid, dim3(256), 0, s, a, tm, 0);                  \
     } while (0)
     if (a.epi == EPI_F32) RL_CUT(EPI_F32);
@@ -1078,7 +1097,7 @@ bool moe_tiles_fit(int npairs, int n_rows, int E, int H, int Fe, int* bm) {
 hipError_t launch_moe_tiles(const MoeArgs& a, int epi, hipStream_t s) {
     if (a.npairs <= 0) return hipSuccess;
     if (a.K % 64 != 0 || (a.bm != 128 && a.bm != 256)) return hipErrorInvalidValue;
-    GemmArgs g{};
+    GemmArgsX g{};
     g.A = a.A; g.lda = a.lda; g.W = a.W; g.ldw = a.ldw; g.M = a.npairs; g.Nw = a.Nw; g.K = a.K; g.epi = epi;
     g.act = a.act; g.ld_act = a.ld_act; g.F = a.F;
     g.g_off = a.off; g.g_toff = a.toff; g.g_tiles = a.tiles; g.g_pairs = a.pairs; g.g_pw = a.pw; g.g_plane = a.plane;
@@ -1088,7 +1107,14 @@ hipError_t launch_moe_tiles(const MoeArgs& a, int epi, hipStream_t s) {
     // at most one part-filled row tile per expert with any pair
     const int m_tiles = a.npairs / a.bm + (a.npairs < a.E ? a.npairs : a.E);
     const dim3 grid((m_tiles * tm.n_tiles + 7) / 8 * 8), block(512);
-#define RL_MOE(BM, SA, EPI) hipLaunchKernelGGL((gemm_dma128_kernel<BM, 256, 2, 8, SA, 3, EPI, 3>), grid, block, 0, s, g, a.K, tm, 0)
+    const bool once = a.npairs / a.E <= a.bm / 2;   // most experts have a single row tile
+#define RL_MOE(BM, SA, EPI)                                                                                            \
+    do {                                                                                                              \
+        if (once)                                                                                                     \
+            hipLaunchKernelGGL((gemm_dma128_kernel<BM, 256, 2, 8, SA, 3, EPI, 3, true>), grid, block, 0, s, g, a.K, tm, 0); \
+        else                                                                                                          \
+            hipLaunchKernelGGL((gemm_dma128_kernel<BM, 256, 2, 8, SA, 3, EPI, 3, false>), grid, block, 0, s, g, a.K, tm, 0); \
+    } while (0)
     if (a.bm == 256) {
         if (epi == EPI_SWIGLU) RL_MOE(256, 2, EPI_SWIGLU);
         else RL_MOE(256, 2, EPI_RESID);
@@ -1100,7 +1126,7 @@ hipError_t launch_moe_tiles(const MoeArgs& a, int epi, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_lse(const GemmArgs& a, hipStream_t s) {
+hipError_t launch_gemm_lse(const GemmArgsX& a, hipStream_t s) {
     if (a.M <= 0) return hipSuccess;
     constexpr int BM = 256, BN = kLseCols, NW = 8;
     constexpr uint64_t kOffLimit = 0xFFFFFFFFull;
@@ -1112,7 +1138,7 @@ hipError_t launch_gemm_lse(const GemmArgs& a, hipStream_t s) {
     tm.n_tiles = (a.Nw + BN - 1) / BN;
     tm.gm = tm.m_tiles < 8 ? tm.m_tiles : 8;
     tm.whole = tm.m_tiles * tm.n_tiles;
-    hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, 2, NW, 2, 3, EPI_LSE, 0>), dim3((tm.whole + 7) / 8 * 8),
+    hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, 2, NW, 2, 3, EPI_LSE, 0, false>), dim3((tm.whole + 7) / 8 * 8),
                        dim3(64 * NW), 0, s, a, a.K, tm, 0);
     return hipGetLastError();
 }

@@ -78,10 +78,12 @@ struct AttnItem {
                     // workspace row qrow_b, partial index part_b (nq = 2,
                     // no key of the chunk is masked for either); -1: none
     int32_t part_b;
-    int32_t pad;    // 1 on the first item of a workgroup whose four items read
-                    // the same shared prompt chunk (same slot and key range):
-                    // the workgroup stages each K/V step through LDS once
+    int32_t flags;  // kAttnLds, kAttnOnce
 };
+constexpr int32_t kAttnLds = 1;    // on the first item of a workgroup whose four items read the same shared
+                                   // prompt chunk (same slot and key range): the workgroup stages each
+                                   // K/V step through LDS once
+constexpr int32_t kAttnOnce = 2;   // no other item of the launch reads these keys
 
 struct GemmArgs {
     const void* A;   int lda;     // [M][K] model dtype
@@ -93,6 +95,11 @@ struct GemmArgs {
     void* act;       int ld_act;  // EPI_SWIGLU output, model dtype
     int F;                        // EPI_SWIGLU
     float* partial;               // [splits][M][Nw] when splits > 1
+};
+
+// What the tile kernel's scoring head and grouped expert launches need beyond
+// that (apart from it, so that every other launch copies fewer argument bytes).
+struct GemmArgsX : GemmArgs {
     float2* lse;                  // EPI_LSE: [column tiles of kLseCols][M]
     float T;                      // EPI_LSE: temperature (> 0)
     // grouped expert projection (launch_moe_tiles): A rows are gathered and
@@ -211,7 +218,8 @@ hipError_t launch_rope_append(int dt, const float* qkv, int splits, int n_rows, 
 
 // ev_start / ev_stop (may be null): events stamped with the kernel's own
 // start and end (attached to the dispatch, not recorded around it)
-hipError_t launch_attention_bf16(const AttnItem* items, int n_items, const void* q,
+// Wave w runs items wave_first[w] .. wave_first[w + 1] - 1 (w < n_waves), or item w when wave_first is null.
+hipError_t launch_attention_bf16(const AttnItem* items, const int32_t* wave_first, int n_waves, const void* q,
                                  const void* kc, const void* vc, const KvPages& kp, int Hq, int Hkv,
                                  int D, int layer, void* out, float* part,
                                  hipStream_t s, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
@@ -273,7 +281,7 @@ hipError_t launch_logprob(const float* logits, int ld, int n_rows, int V, const 
                           const int32_t* item_idx, const int32_t* targets, float T, float* out,
                           hipStream_t s);
 
-hipError_t launch_gemm_lse(const GemmArgs& a, hipStream_t s);   // bf16, K % 64 == 0, operands under 4 GiB
+hipError_t launch_gemm_lse(const GemmArgsX& a, hipStream_t s);   // bf16, K % 64 == 0, operands under 4 GiB
 // The same values as launch_logprob from the column tiles of launch_gemm_lse
 // ([n_tiles][n_rows]): h [n_rows][H] and w [V][H] are the head's operands.
 hipError_t launch_logprob_lse(const float2* lse, int n_tiles, int n_rows, const void* h, const void* w, int H, int V,
