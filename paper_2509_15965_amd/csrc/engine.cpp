@@ -1512,10 +1512,10 @@ rl_status build_runs(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks
 
 // Prefill / scoring tiles: each block run of consecutive query tokens of one
 // sequence (blocks of one slot with consecutive rows and positions) split
-// into tiles of kPrefillWaves * (16 / G) tokens, longest key range first.
+// into tiles of prefill_waves(G) * (32 / G) tokens, longest key range first.
 rl_status build_tiles(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks, Fwd* f) {
     const int G = c->cfg.n_q_heads / c->cfg.n_kv_heads;
-    const int T = kPrefillWaves * std::max(1, 16 / G);
+    const int T = prefill_waves(G) * (32 / G);
     std::vector<PrefillTile> tl;
     size_t i = 0;
     while (i < blocks.size()) {

@@ -146,6 +146,13 @@ __device__ __forceinline__ int kswz(int r) {
     return D == 128 ? ((r & 3) | ((r >> 1) & 12)) : (((r >> 1) & 1) | ((r >> 2) & 6));
 }
 
+// The same for the 32-row fragment reads of the prefill kernel, whose lane
+// groups read 16 consecutive positions.
+template <int D>
+__device__ __forceinline__ int kswz32(int r) {
+    return D == 128 ? (r & 15) : ((r >> 1) & 7);
+}
+
 __device__ __forceinline__ void lds_dma16(const void* g, uint8_t* lds_wave_base) {
     __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)(lds_wave_base), 16, 0, 0);
 }
@@ -155,7 +162,7 @@ __device__ __forceinline__ void lds_dma16(const void* g, uint8_t* lds_wave_base)
 // kWaves waves of the workgroup: wave w moves KB w, w + kWaves, ... of each
 // (waves past the step's KB count move none).  One global_load_lds per KB per
 // lane.
-template <int D, int kWaves>
+template <int D, int kWaves, bool kRows32 = false>
 __device__ __forceinline__ void step_dma(const uint16_t* kb, const uint16_t* vb, int t0, int wave, int lane,
                                          uint8_t* kl, uint8_t* vl) {
     constexpr int STEPB = 32 * D * 2;
@@ -167,7 +174,7 @@ __device__ __forceinline__ void step_dma(const uint16_t* kb, const uint16_t* vb,
         const int kb_ = wave + kWaves * j;
         if (kb_ >= NKB) break;
         const int r = kb_ * RPK + lane / CPR;
-        const int c = (lane % CPR) ^ kswz<D>(r);
+        const int c = (lane % CPR) ^ (kRows32 ? kswz32<D>(r) : kswz<D>(r));
         lds_dma16(kb + static_cast<size_t>(t0 + r) * D + 8 * c, kl + kb_ * 1024);
         lds_dma16(reinterpret_cast<const uint8_t*>(vb + static_cast<size_t>(t0) * D) + kb_ * 1024 + lane * 16,
                   vl + kb_ * 1024);
@@ -385,33 +392,39 @@ hipError_t launch_attention_bf16(const AttnItem* items, const int32_t* wave_firs
 
 
 // ---------------------------------------------------------------------------
-// Prefill / scoring attention: a workgroup of kPrefillWaves waves shares each
-// K/V step through LDS.  Per 32-position step the workgroup DMAs the step's K rows
-// ([32][D], 16-byte chunks permuted by row so that the fragment reads below
-// are free of bank conflicts) and its four V blocks ([4][D][8], contiguous in
-// the cache) into one of two LDS buffers with global_load_lds; every wave
-// then runs the decode kernel's MFMA step on its own 16 query columns from
-// LDS.  The next step's DMA is issued right after the barrier that retires
-// the previous step, so it overlaps the current step's math.
+// Prefill / scoring attention: a workgroup of WAVES waves shares each
+// K/V step through LDS, each wave with its own kPrefillCols query columns
+// (tokens x the q-heads of one kv-head).  Per 32-position step the workgroup
+// DMAs the step's K rows ([32][D], 16-byte chunks permuted by row so that the
+// fragment reads are free of bank conflicts) and its four V blocks
+// ([4][D][8], contiguous in the cache) into one of two LDS buffers with
+// global_load_lds, the next step's right after the barrier that retires the
+// previous one.  32x32x16 MFMAs: a wave's fragment reads (16 KB a step at D =
+// 128) then serve 32 columns; with 16 columns and 16x16x32 MFMAs those reads
+// bound the kernel (20.8k rows of one 7B group, 640 + 16 x 1100 tokens: 1748 ->
+// 1057 us a layer).  K rows are read in the order that leaves each lane with
+// the scores of the eight consecutive positions its P.V operand takes: output
+// row 8q + 4h + i of the score tile is position 16(q/2) + 8h + 4(q%2) + i.
 // ---------------------------------------------------------------------------
+constexpr int kPrefillCols = 32;
 
-template <int D>
-__global__ void __launch_bounds__(64 * kPrefillWaves) attn_prefill_kernel(const PrefillTile* __restrict__ tiles,
+template <int D, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) attn_prefill_kernel(const PrefillTile* __restrict__ tiles,
         const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
         KvPages kp, int Hq, int Hkv, int layer, float scale_log2, uint16_t* __restrict__ out) {
-    constexpr int KG = D / 32, DT = D / 16;
+    constexpr int KS = D / 16, DT = D / 32;
     constexpr int STEPB = 32 * D * 2;               // bytes of K (and of V) per 32-position step
     static_assert(STEPB % 1024 == 0, "whole 1 KB DMA instructions per step");
     __shared__ __attribute__((aligned(1024))) uint8_t lds[2][2][STEPB];   // [buffer][K | V]
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int kvh = blockIdx.y;
     const int G = Hq / Hkv;
-    const int tq = 16 / G;
+    const int tq = kPrefillCols / G;
     const PrefillTile tl = tiles[blockIdx.x];
     const int tok0 = wave * tq;
     const int nq = max(0, min(tq, tl.ntok - tok0));
-    const int col = lane & 15, kq = lane >> 4;
+    const int col = lane & 31, kh = lane >> 5;
     const bool cvalid = col < nq * G;
     const int tau = cvalid ? col / G : 0;
     const int head = kvh * G + (cvalid ? col - tau * G : 0);
@@ -419,27 +432,32 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) attn_prefill_kernel(const 
     const int limit = cvalid ? tl.pos0 + tok0 + tau : -1;
     const int hi = tl.pos0 + tl.ntok;               // keys [0, hi)
     const int wave_last = tl.pos0 + tok0 + nq - 1;  // last key any column of this wave sees
+    const int full_end = min(hi, tl.pos0 + tok0 + 1);   // steps that end here mask nothing
     const int nsteps = (hi + 31) / 32;
 
     // the K/V of the step at position t0: its page's blocks and t0 inside the page
     auto dma_step = [&](int t0, int buf) {
         int lt;
         const size_t b = kv_block(kp, layer, Hkv, kv_page(kp, tl.slot, t0, &lt), kvh);
-        step_dma<D, kPrefillWaves>(kc + b, vc + b, lt, wave, lane, lds[buf][0], lds[buf][1]);
+        step_dma<D, WAVES, true>(kc + b, vc + b, lt, wave, lane, lds[buf][0], lds[buf][1]);
     };
 
     const u32x4 zero = {0u, 0u, 0u, 0u};
-    u32x4 qf[KG];
+    u32x4 qf[KS];
     {
-        const uint16_t* qp = q + (static_cast<size_t>(qrow) * Hq + head) * D + 8 * kq;
+        const uint16_t* qp = q + (static_cast<size_t>(qrow) * Hq + head) * D + 8 * kh;
 #pragma unroll
-        for (int j = 0; j < KG; ++j) qf[j] = cvalid ? ld16(qp + 32 * j) : zero;
+        for (int j = 0; j < KS; ++j) qf[j] = cvalid ? ld16(qp + 16 * j) : zero;
     }
     float m = -INFINITY, l = 0.0f;
-    f32x4 o[DT];
+    f32x16 o[DT];
 #pragma unroll
-    for (int i = 0; i < DT; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int krow = 8 * (col >> 2) + (col & 3);
+    for (int i = 0; i < DT; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[i][e] = 0.f;
+    // the position in the step that this lane's K row holds, and its LDS bytes
+    const int kpos = 16 * (col >> 4) + 8 * ((col >> 2) & 1) + 4 * ((col >> 3) & 1) + (col & 3);
+    const int krow = kpos * (2 * D), kx = kswz32<D>(kpos);
 
     if (nsteps > 0) dma_step(0, 0);
     for (int s = 0; s < nsteps; ++s) {
@@ -448,23 +466,74 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) attn_prefill_kernel(const 
         if (s + 1 < nsteps) dma_step(32 * (s + 1), (s + 1) & 1);
         const int t0 = 32 * s;
         if (nq == 0 || t0 > wave_last) continue;       // wave-uniform: nothing of this step is visible
-        u32x4 k0[KG], k1[KG], vf[DT];
-        step_frags<D>(lds[s & 1][0], lds[s & 1][1], krow, kq, col, k0, k1, vf);
-        attn_step<D>(k0, k1, vf, qf, t0, hi, limit, t0 + 32 <= tl.pos0 + tok0 + 1, kq, scale_log2, m, l, o);
+        const uint8_t *kl = lds[s & 1][0], *vl = lds[s & 1][1];
+        f32x16 sc;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sc[e] = 0.f;
+#pragma unroll
+        for (int j = 0; j < KS; ++j) {
+            const u32x4 kf = *reinterpret_cast<const u32x4*>(kl + krow + 16 * ((2 * j + kh) ^ kx));
+            sc = mfma32x32x16(as_bf16x8(kf), as_bf16x8(qf[j]), sc);
+        }
+        // this lane holds the scores of its column at positions t0 + 16(e/8) + 8 kh + e%8
+        const bool full = t0 + 32 <= full_end;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sc[e] *= scale_log2;
+        if (!full) {
+            const int lim = min(hi - 1, limit) - t0 - 8 * kh;
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (16 * (e >> 3) + (e & 7) > lim) sc[e] = -INFINITY;
+        }
+        float mx = sc[0];
+#pragma unroll
+        for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sc[e]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float m_new = fmaxf(m, mx);
+        const float m_use = m_new == -INFINITY ? 0.0f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f(m - m_use);
+        // probabilities as a bf16 pair hi + lo (~16 significant bits)
+        float psum = 0.0f;
+        u32x4 ph[2], pl[2];
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+            const float p0 = __builtin_amdgcn_exp2f(sc[2 * w] - m_use);
+            const float p1 = __builtin_amdgcn_exp2f(sc[2 * w + 1] - m_use);
+            psum += p0 + p1;
+            const uint32_t h = pack_bf16(p0, p1);
+            ph[w >> 2][w & 3] = h;
+            pl[w >> 2][w & 3] = pack_bf16(p0 - __uint_as_float(h << 16), p1 - __uint_as_float(h & 0xFFFF0000u));
+        }
+        l = l * alpha + psum;
+        m = m_new;
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {   // a new maximum: rare after the first steps
+#pragma unroll
+            for (int i = 0; i < DT; ++i) o[i] = o[i] * alpha;
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int nvalid = hi - (t0 + 16 * c + 8 * kh);   // keys past the end carry no data
+#pragma unroll
+            for (int i = 0; i < DT; ++i) {
+                u32x4 v = *reinterpret_cast<const u32x4*>(vl + ((2 * c + kh) * D + 32 * i + col) * 16);
+                if (!full && nvalid < 8) v = mask_tail8(v, nvalid < 0 ? 0 : nvalid);
+                o[i] = mfma32x32x16(as_bf16x8(v), as_bf16x8(ph[c]), o[i]);
+                o[i] = mfma32x32x16(as_bf16x8(v), as_bf16x8(pl[c]), o[i]);
+            }
+        }
     }
-    l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
     if (!cvalid) return;
     const float inv = 1.0f / l;
-    uint16_t* op = out + (static_cast<size_t>(qrow) * Hq + head) * D + 4 * kq;
+    uint16_t* op = out + (static_cast<size_t>(qrow) * Hq + head) * D + 4 * kh;
+    // lane holds O^T[d = 32 i + 8 w + 4 kh + e][col]
 #pragma unroll
-    for (int i = 0; i < DT; ++i) {
-        const uint32_t w0 = static_cast<uint32_t>(f32_to_bf16(o[i][0] * inv)) |
-                            (static_cast<uint32_t>(f32_to_bf16(o[i][1] * inv)) << 16);
-        const uint32_t w1 = static_cast<uint32_t>(f32_to_bf16(o[i][2] * inv)) |
-                            (static_cast<uint32_t>(f32_to_bf16(o[i][3] * inv)) << 16);
-        *reinterpret_cast<uint2*>(op + 16 * i) = make_uint2(w0, w1);
-    }
+    for (int i = 0; i < DT; ++i)
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            *reinterpret_cast<uint2*>(op + 32 * i + 8 * w) =
+                make_uint2(pack_bf16(o[i][4 * w] * inv, o[i][4 * w + 1] * inv),
+                           pack_bf16(o[i][4 * w + 2] * inv, o[i][4 * w + 3] * inv));
 }
 
 hipError_t launch_attention_prefill(const PrefillTile* tiles, int n_tiles, const void* q, const void* kc,
@@ -472,15 +541,18 @@ hipError_t launch_attention_prefill(const PrefillTile* tiles, int n_tiles, const
                                     void* out, hipStream_t s) {
     if (n_tiles <= 0) return hipSuccess;
     const float scale_log2 = 1.4426950408889634f / sqrtf(static_cast<float>(D));
-    dim3 grid(n_tiles, Hkv), block(64 * kPrefillWaves);
-    if (D == 128)
-        hipLaunchKernelGGL(attn_prefill_kernel<128>, grid, block, 0, s, tiles, static_cast<const uint16_t*>(q),
+    const int waves = prefill_waves(Hq / Hkv);
+    const dim3 grid(n_tiles, Hkv), block(64 * waves);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, block, 0, s, tiles, static_cast<const uint16_t*>(q),
                            static_cast<const uint16_t*>(kc), static_cast<const uint16_t*>(vc), kp, Hq, Hkv,
                            layer, scale_log2, static_cast<uint16_t*>(out));
-    else
-        hipLaunchKernelGGL(attn_prefill_kernel<64>, grid, block, 0, s, tiles, static_cast<const uint16_t*>(q),
-                           static_cast<const uint16_t*>(kc), static_cast<const uint16_t*>(vc), kp, Hq, Hkv,
-                           layer, scale_log2, static_cast<uint16_t*>(out));
+    };
+    if (waves == 4) {
+        if (D == 128) go(attn_prefill_kernel<128, 4>); else go(attn_prefill_kernel<64, 4>);
+    } else {
+        if (D == 128) go(attn_prefill_kernel<128, 8>); else go(attn_prefill_kernel<64, 8>);
+    }
     return hipGetLastError();
 }
 
