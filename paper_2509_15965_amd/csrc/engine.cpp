@@ -760,7 +760,13 @@ rl_status run_moe(rl_decode_ctx* c, int l, int n, const void* h) {
 
 // Scoring passes of more LM-head rows than this reduce the logits inside the
 // head's 256 x 256 tiles; fewer go through the decode kernels and a logits buffer.
+// An override decides by its kernel, whatever the row count: with one kernel for
+// every size, a sequence's scores do not depend on what is scored beside it.
 constexpr int kFusedHeadRows = 128;
+bool fused_head(const rl_decode_ctx* c, int rows) {
+    if (!c->bf16() || c->cfg.hidden % 64 != 0) return false;
+    return c->opt_gemm == 0 ? rows > kFusedHeadRows : c->opt_gemm == RL_GEMM_T256;
+}
 
 rl_status run_forward(rl_decode_ctx* c, const Fwd& f) {
     const rl_model_config& cf = c->cfg;
@@ -876,7 +882,7 @@ rl_status run_forward(rl_decode_ctx* c, const Fwd& f) {
         if (e != hipSuccess) return hip_fail(c, e, "final rmsnorm launch");
         pr.done(nf * H * (4.0 + es) + H * es, 0.0);
     }
-    if (f.score_items && c->bf16() && H % 64 == 0 && nf > kFusedHeadRows) {
+    if (f.score_items && fused_head(c, nf)) {
         // rows whose column tiles (one float2 per row and kLseCols logits) fit the split-K partials
         const int V = cf.vocab, n_tiles = ceil_div(V, kLseCols);
         const size_t fit = L.part_floats / 2 / n_tiles;

@@ -6,7 +6,7 @@ import torch
 
 from paper_2509_15965_amd.configs import ModelShape
 from paper_2509_15965_amd.inputs import make_weights
-from paper_2509_15965_amd.rl_decode import RL_GEMM_T128, RL_OPT_GEMM_PLAN, Engine, gemm_plan_code
+from paper_2509_15965_amd.rl_decode import RL_GEMM_T128, RL_GEMM_T256, RL_OPT_GEMM_PLAN, Engine, gemm_plan_code
 
 pytestmark = pytest.mark.gpu
 
@@ -35,9 +35,11 @@ def test_head_in_tiles(vocab, rlens, T):
     resp = [rng.integers(0, vocab, m).astype(np.int32) for m in rlens]
     resp[0][3], resp[1][0] = -1, vocab   # not scored: NaN
     eng = Engine(shape, w, max_seqs=len(rlens), max_ctx=160, max_prefill_tokens=1024)
-    # one tile kernel for every row count: the hidden states are then the same bits in both calls
-    eng.set_option(RL_OPT_GEMM_PLAN, gemm_plan_code(RL_GEMM_T128))
+    # tile kernels for every row count, both adding up K in the same order: the hidden states are then the same
+    # bits in both calls, and the 256 x 256 one reduces the logits in its tiles
+    eng.set_option(RL_OPT_GEMM_PLAN, gemm_plan_code(RL_GEMM_T256))
     together = score(eng, prompts, group, resp, T)
+    eng.set_option(RL_OPT_GEMM_PLAN, gemm_plan_code(RL_GEMM_T128))
     alone = np.concatenate([score(eng, [prompts[i // group]], 1, [resp[i]], T) for i in range(len(resp))])
     eng.close()
     assert np.array_equal(np.isnan(together), np.isnan(alone)) and np.isnan(alone).sum() == 2
