@@ -35,7 +35,7 @@ namespace {
 struct TileKernel { int variant, BM, BN, per_cu; double t_round, t_alone; };
 constexpr TileKernel kLineTiles[] = {   // ties go to the earlier entry (weights not cache resident)
     {kLineVariant256x256, 256, 256, 1, 31.0, 31.0},
-    {kLineVariant128x128, 128, 128, 2, 20.3, 15.0},
+    {kLineVariant128x128, 128, 128, 2, 20.3, 12.0},
     {kLineVariant128x256, 128, 256, 1, 19.5, 19.5},
     {kLineVariant128x128Deep, 128, 128, 1, 12.0, 12.0},
 };
@@ -132,6 +132,26 @@ GemmPlan plan_gemm_bf16(int M, int Nw, int K, int epi, int F) {
             best = us;
             best_p = GemmPlan{};
             best_p.variant = kGemvVariant; best_p.splits = 1; best_p.ksplit = K;
+        }
+    }
+    if (M <= 16 && K % 64 == 0 && epi != EPI_SWIGLU && wbytes <= 40.0e6) {
+        // Wide GEMV: K cut over workgroups of 64 weight rows.  Pays where 16-row
+        // workgroups of a whole K are too few or one and a bit per CU (11 rows:
+        // q|k|v 4608 x 3584 16.8 -> 10 us, o 3584 x 3584 11.4 -> 7; one row: down
+        // 1536 x 8960 10.1 us and 28 slices in the direct form, 7 us and 8 here);
+        // larger weights stream better in the other forms (11 rows, down 3584 x
+        // 18944: 37 us with its consumer here, 33 in split tiles).
+        for (int s = 1; s <= 8; s *= 2) {
+            const int ks = ceil_div(ceil_div(K, s), 64) * 64;
+            if (s > 1 && (ks < 256 || static_cast<size_t>(ceil_div(K, ks)) * M * Nw > kPartCapFloats)) break;
+            const long per_cu = (static_cast<long>(ceil_div(Nw, 64)) * ceil_div(K, ks) + kCUs - 1) / kCUs;
+            const double us = per_cu * (64.0 * ks * 2.0 * (1.0 + 0.65 * M / 64.0)) / 24.0e3 + 3.0 + out_us +
+                              (s > 1 ? 8.0 * s * M * static_cast<double>(Nw) / 3.0e6 + (epi == EPI_RESID ? 1.0 : 2.0) : 0.0);
+            if (us < best * 0.95) {
+                best = us;
+                best_p = GemmPlan{};
+                best_p.variant = kGemvWideVariant; best_p.ksplit = ks; best_p.splits = ceil_div(K, ks);
+            }
         }
     }
     if (K % 64 != 0) {
