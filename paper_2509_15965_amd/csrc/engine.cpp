@@ -168,6 +168,14 @@ Layout make_layout(const rl_model_config& c) {
     return L;
 }
 
+// Weights a decode step reads (every expert of a mixture).
+double step_weight_bytes(const rl_model_config& c) {
+    const double H = c.hidden, qd = static_cast<double>(c.n_q_heads) * c.head_dim, kd = static_cast<double>(c.n_kv_heads) * c.head_dim;
+    const double mlp = c.n_experts > 0 ? c.n_experts * (H + 3.0 * H * c.expert_ffn) : 3.0 * H * c.ffn;
+    return (c.n_layers * (H * (2.0 * qd + 2.0 * kd) + mlp) + H * c.vocab) * (c.dtype == RL_DTYPE_BF16 ? 2 : 4);
+}
+constexpr double kMemSideCache = 256.0 * (1 << 20);
+
 }  // namespace
 
 struct rl_decode_ctx {
@@ -179,6 +187,7 @@ struct rl_decode_ctx {
     uint8_t* ws = nullptr;
     hipStream_t stream = nullptr;
     int device = 0;
+    bool w_cached = false;            // all weights a step reads fit kMemSideCache: they stay there from step to step
     std::vector<int32_t> len;
     // shared GRPO prompt: decode attention over positions [0, share_len[s])
     // of slot s reads slot share_src[s] (the group's first slot, holding the
@@ -604,6 +613,7 @@ rl_status run_gemm_plan(rl_decode_ctx* c, int kc, const GemmPlan* plan, const vo
     a.A = A; a.lda = lda; a.W = W; a.ldw = K; a.M = M; a.Nw = Nw; a.K = K; a.epi = epi;
     a.out_f32 = out_f32; a.ldo = ldo; a.resid = resid; a.ldr = ldr; a.act = act; a.ld_act = ld_act;
     a.F = cf.ffn;
+    a.w_cached = c->w_cached;
     a.partial = c->wsp<float>(c->lay.off_part);
     const double es = c->lay.es;
     const int n_out = epi == EPI_SWIGLU ? cf.ffn : Nw;
@@ -732,6 +742,7 @@ rl_status run_moe(rl_decode_ctx* c, int l, int n, const void* h) {
     a.E = E; a.k = k; a.n_rows = n; a.npairs = n * k;
     a.off = off; a.pairs = pairs; a.pw = pw;
     a.bm = bm; a.toff = toff; a.tiles = tiles;
+    a.w_cached = c->w_cached;
     {
         Prof pr(c, RL_K_MOE_EXPERTS);
         MoeArgs g = a;   // gate|up: token rows -> SwiGLU rows of the pairs
@@ -1438,6 +1449,7 @@ rl_status build_items(rl_decode_ctx* c, Meta* m, const std::vector<Block>& block
 // remainder, where the longest item decided; 48 rows of 1000-6000, 32B: 125 us
 // against 153; 131 rows of 300-1300 on pages, mixture of experts: 47 against 77).
 constexpr int kCutSnap = 16;      // 1 / 16 of a run
+constexpr double kStreamKeyBytes = 16e6;
 constexpr int kMinRunSteps = 2;   // fewer rows: a run still holds 64 keys
 rl_status build_runs(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks, Fwd* f) {
     const int Hkv = c->cfg.n_kv_heads;
@@ -1455,6 +1467,9 @@ rl_status build_runs(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks
     waves = std::min(waves, total * (kMaxCombine - 2) / longest);   // a row is cut into at most kMaxCombine items
     waves = std::max<int64_t>(waves, 1);
     const int64_t snap = total / waves / kCutSnap;
+    // keys of a layer too few to displace anything keep to the caches
+    const bool large = 32.0 * total * Hkv * c->cfg.head_dim * 2 * c->lay.es >= kStreamKeyBytes;
+    const int32_t stream = large ? kAttnOnce : 0;
     AttnItem* dItems = nullptr;
     const size_t cap = blocks.size() + static_cast<size_t>(waves);
     if (cap > static_cast<size_t>(c->lay.items_cap)) return fail(c, RL_ERR_CAPACITY, "too many attention work items");
@@ -1484,7 +1499,7 @@ rl_status build_runs(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks
             it.kv_lo = static_cast<int>(at - pos) * 32;
             it.kv_hi = std::min<int>(hi, static_cast<int>(to - pos) * 32);
             it.part = -1; it.qrow_b = -1; it.part_b = -1;
-            it.flags = kAttnOnce;
+            it.flags = stream;
             at = to;
             // a run that ends just past a row's end ends there
             if (at == row_end && n_waves < waves && wave_end - at <= snap) wave_end = at;
@@ -1690,6 +1705,7 @@ rl_status rl_decode_create(const rl_model_config* cfg, const rl_weights* w, void
     c->cfg = *cfg;
     c->w = *w;
     c->lay = L;
+    c->w_cached = step_weight_bytes(*cfg) <= kMemSideCache;
     c->kv = static_cast<uint8_t*>(kv_pool);
     c->ws = static_cast<uint8_t*>(workspace);
     c->stream = static_cast<hipStream_t>(stream);

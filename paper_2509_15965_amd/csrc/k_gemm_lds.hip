@@ -945,7 +945,7 @@ hipError_t launch_dma128(const GemmArgs& a, const GemmPlan& p, int n0, int n1, h
     const dim3 grid = tm.xsplit ? dim3(8 * tm.whole, p.splits / 8) : dim3((tm.whole + 7) / 8 * 8, p.splits);
 #define RL_DMA(EPI, MODE)                                                                                              \
     do {                                                                                                              \
-        if (tm.m_tiles == 1)                                                                                          \
+        if (tm.m_tiles == 1 && !a.w_cached)                                                                                      \
             hipLaunchKernelGGL((gemm_dma128_kernel<BM, BN, WM, NW, SA, SW, EPI, MODE, true>), grid, block, 0, s, a,    \
                                p.ksplit, tm, n0);                                                                     \
         else                                                                                                          \
@@ -1107,7 +1107,7 @@ hipError_t launch_moe_tiles(const MoeArgs& a, int epi, hipStream_t s) {
     // at most one part-filled row tile per expert with any pair
     const int m_tiles = a.npairs / a.bm + (a.npairs < a.E ? a.npairs : a.E);
     const dim3 grid((m_tiles * tm.n_tiles + 7) / 8 * 8), block(512);
-    const bool once = a.npairs / a.E <= a.bm / 2;   // most experts have a single row tile
+    const bool once = a.npairs / a.E <= a.bm / 2 && !a.w_cached;   // most experts have a single row tile
 #define RL_MOE(BM, SA, EPI)                                                                                            \
     do {                                                                                                              \
         if (once)                                                                                                     \

@@ -94,6 +94,7 @@ struct GemmArgs {
     float* resid;    int ldr;     // EPI_RESID
     void* act;       int ld_act;  // EPI_SWIGLU output, model dtype
     int F;                        // EPI_SWIGLU
+    int w_cached;                 // the model's weights fit the memory-side cache: no non-temporal weight loads
     float* partial;               // [splits][M][Nw] when splits > 1
 };
 
@@ -136,6 +137,7 @@ struct MoeArgs {
     const int32_t* toff;                   // [E + 1] row tiles (bm pairs each) before every expert's (launch_moe_tiles)
     const int32_t* tiles;                  // expert of every row tile, at most npairs / bm + E of them
     int bm;                                // rows of a row tile: 128 or 256
+    int w_cached;                          // as GemmArgs::w_cached
 };
 
 struct GemmPlan {
