@@ -906,6 +906,7 @@ rl_status run_forward(rl_decode_ctx* c, const Fwd& f) {
             a.A = hr; a.lda = H; a.W = c->w.lm_head; a.ldw = H; a.M = nc; a.Nw = V; a.K = H; a.epi = EPI_LSE;
             a.lse = c->wsp<float2>(L.off_part);
             a.T = f.T;
+            a.row_items = f.score_items + r0; a.item_idx = f.score_idx; a.targets = f.score_targets; a.out_logp = f.out_logp;
             {
                 Prof pr(c, RL_K_GEMM_LM_HEAD);
                 e = launch_gemm_lse(a, c->stream);
@@ -913,10 +914,9 @@ rl_status run_forward(rl_decode_ctx* c, const Fwd& f) {
                 pr.done(es * V * H + es * nc * H + 8.0 * nc * n_tiles, 2.0 * nc * V * H);
             }
             Prof pr(c, RL_K_SAMPLE);
-            e = launch_logprob_lse(a.lse, n_tiles, nc, hr, c->w.lm_head, H, V, f.score_items + r0, f.score_idx,
-                                   f.score_targets, f.T, f.out_logp, c->stream);
+            e = launch_logprob_lse(a.lse, n_tiles, nc, V, a.row_items, f.score_idx, f.score_targets, f.out_logp, c->stream);
             if (e != hipSuccess) return hip_fail(c, e, "log-prob launch");
-            pr.done(8.0 * nc * n_tiles + 4.0 * nc * H, 0.0);
+            pr.done(8.0 * nc * n_tiles + 8.0 * nc, 0.0);
         }
         return RL_OK;
     }
@@ -2044,12 +2044,12 @@ rl_status rl_score(rl_decode_ctx* ctx, int32_t n_prompts, int32_t group, const i
     f.out_logp = out_logp;
     f.score_items = d_items;
     f.score_idx = d_idx;
-    f.score_targets = resp_tokens;
     set_group_pages(c, n_prompts, group, slots, plens, new_len);
     f.kvp = fill_pages(c, ps);
     st = upload_meta(c, &m, stage);
     if (st != RL_OK) return st;
     int32_t* tok = c->wsp<int32_t>(c->lay.off_tok);
+    f.score_targets = tok + R1;   // this call's copy: out_logp is written before the last read of the targets
     hipError_t e = hipMemcpyAsync(tok, prompt_tokens, sizeof(int32_t) * R1, hipMemcpyDeviceToDevice, c->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(tok + R1, resp_tokens, sizeof(int32_t) * static_cast<size_t>(r2), hipMemcpyDeviceToDevice,

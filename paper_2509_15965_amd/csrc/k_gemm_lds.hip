@@ -808,13 +808,28 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(
         // time go through LDS (the ring is free by then) so that two lanes
         // hold a row's 64 columns of this wave; the four waves of a row meet
         // in LDS.  About 4% of a tile of K 3584, against 13% for storing the
-        // tile's logits and 8% for reading them back.
-        static_assert(NT == 2 && WN == 4 && BN == kLseCols, "row reduction layout");
+        // tile's logits and 8% for reading them back.  A target's logit leaves
+        // from here too, the number that entered its row's sum: the log-sum-exp
+        // is then never below it, and no log-probability above 0.
+        static_assert(NT == 2 && WN == 4 && BN == kLseCols && TM == 128, "row reduction layout");
         constexpr int LDZ = 68;   // floats per row: 16-byte aligned, reads free of bank conflicts
         static_assert(NW * 32 * LDZ * 4 + WN * BM * 8 <= SA * ASTAGE + SW * BSTAGE, "LDS");
         float* zs = reinterpret_cast<float*>(smem) + wave * 32 * LDZ;
         float2* part = reinterpret_cast<float2*>(smem + NW * 32 * LDZ * 4);   // [WN][BM]
-        const int c0 = n_tile * BN + wn * TN + (lane & 1) * 32;   // this lane's 32 columns
+        const int cw = n_tile * BN + wn * TN;     // this wave's 64 columns
+        const int c0 = cw + (lane & 1) * 32;      // this lane's 32
+        // items of this wave's rows l and l + 64 (l: the lane): first one, count, index and target of the first
+        int it0[2], itn[2], idx0[2], tgt0[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int m = m0 + wm * TM + 64 * u + lane;
+            it0[u] = m < M ? p.row_items[m] : 0;
+            itn[u] = m < M ? p.row_items[m + 1] - it0[u] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) idx0[u] = itn[u] > 0 ? p.item_idx[it0[u]] : 0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) tgt0[u] = itn[u] > 0 ? p.targets[idx0[u]] : -1;
         __syncthreads();   // every wave is done with the ring
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
@@ -856,6 +871,15 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(
                 for (int e = 0; e < 4; ++e) s += __expf(z[q][e] - m_use);
             s += __shfl_xor(s, 1, 64);
             if ((lane & 1) == 0) part[wn * BM + wm * TM + 32 * i + (lane >> 1)] = make_float2(m, s);
+            // the row's targets among this wave's columns: lane l & 1 of its pair takes items l & 1, l & 1 + 2, ...
+            const int from = 32 * (i & 1) + (lane >> 1), n_it = __shfl(itn[i >> 1], from, 64);
+            const int it = __shfl(it0[i >> 1], from, 64), idx_a = __shfl(idx0[i >> 1], from, 64);
+            const int tgt_a = __shfl(tgt0[i >> 1], from, 64);
+            for (int k = lane & 1; k < n_it; k += 2) {
+                const int idx = k == 0 ? idx_a : p.item_idx[it + k];
+                const int y = k == 0 ? tgt_a : p.targets[idx];
+                if (y >= cw && y < cw + TN && y < Nw) p.out_logp[idx] = zs[(lane >> 1) * LDZ + y - cw] / p.T;
+            }
             __builtin_amdgcn_wave_barrier();   // zs is rewritten for the next 32 rows
         }
         __syncthreads();

@@ -324,15 +324,13 @@ hipError_t launch_logprob(const float* logits, int ld, int n_rows, int V, const 
 
 // Log-probabilities from the scoring head's column tiles: a workgroup merges
 // the tiles of kLseRows rows (in tile order within each of 16 lane groups,
-// then the groups in order), then each wave takes rows in turn and computes
-// every target's logit as the dot product h . w_y, which is all of the logits
-// that is needed (18.8k rows x 152064: 8.5 GB of logits neither written nor
-// read).  Latency bound: a few loads per item.
+// then the groups in order) and subtracts each row's log-sum-exp from its
+// items' logits, which the head left in `out`.  Latency bound: a few loads
+// per lane.
 constexpr int kLseRows = 16;
-__global__ void __launch_bounds__(256) logprob_lse_kernel(const float2* __restrict__ lse, int n_tiles, int n_rows,
-        const uint16_t* __restrict__ h, const uint16_t* __restrict__ w, int H, int V,
+__global__ void __launch_bounds__(256) logprob_lse_kernel(const float2* __restrict__ lse, int n_tiles, int n_rows, int V,
         const int32_t* __restrict__ row_items, const int32_t* __restrict__ item_idx,
-        const int32_t* __restrict__ targets, float T, float* __restrict__ out) {
+        const int32_t* __restrict__ targets, float* __restrict__ out) {
     __shared__ Lse part[16][kLseRows];
     __shared__ float row_lse[kLseRows];
     const int r0 = blockIdx.x * kLseRows;
@@ -359,39 +357,20 @@ __global__ void __launch_bounds__(256) logprob_lse_kernel(const float2* __restri
         }
         __syncthreads();
     }
-    const int lane = threadIdx.x & 63;
-    for (int r = r0 + (threadIdx.x >> 6); r < min(r0 + kLseRows, n_rows); r += 4) {
-        const uint16_t* hr = h + static_cast<size_t>(r) * H;
-        for (int k = row_items[r]; k < row_items[r + 1]; ++k) {
-            const int idx = item_idx[k];
-            const int y = targets[idx];
-            if (y < 0 || y >= V) {
-                if (lane == 0) out[idx] = __builtin_nanf("");
-                continue;
-            }
-            const uint16_t* wy = w + static_cast<size_t>(y) * H;
-            float acc = 0.0f;
-            for (int c = 8 * lane; c < H; c += 512) {   // H is a multiple of 8
-                const u32x4 a = ld16(hr + c), b = ld16(wy + c);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    acc = fmaf(__uint_as_float(a[e] << 16), __uint_as_float(b[e] << 16), acc);
-                    acc = fmaf(__uint_as_float(a[e] & 0xFFFF0000u), __uint_as_float(b[e] & 0xFFFF0000u), acc);
-                }
-            }
-            acc = wave_sum(acc);
-            if (lane == 0) out[idx] = acc / T - row_lse[r - r0];
-        }
+    const int r = threadIdx.x / 16;   // 16 lanes a row
+    if (r0 + r >= n_rows) return;
+    for (int k = row_items[r0 + r] + threadIdx.x % 16; k < row_items[r0 + r + 1]; k += 16) {
+        const int idx = item_idx[k];
+        const int y = targets[idx];
+        out[idx] = y >= 0 && y < V ? out[idx] - row_lse[r] : __builtin_nanf("");
     }
 }
 
-hipError_t launch_logprob_lse(const float2* lse, int n_tiles, int n_rows, const void* h, const void* w, int H, int V,
-                              const int32_t* row_items, const int32_t* item_idx, const int32_t* targets, float T,
-                              float* out, hipStream_t s) {
+hipError_t launch_logprob_lse(const float2* lse, int n_tiles, int n_rows, int V, const int32_t* row_items,
+                              const int32_t* item_idx, const int32_t* targets, float* out, hipStream_t s) {
     if (n_rows <= 0) return hipSuccess;
     hipLaunchKernelGGL(logprob_lse_kernel, dim3((n_rows + kLseRows - 1) / kLseRows), dim3(256), 0, s, lse, n_tiles,
-                       n_rows, static_cast<const uint16_t*>(h), static_cast<const uint16_t*>(w), H, V, row_items,
-                       item_idx, targets, T, out);
+                       n_rows, V, row_items, item_idx, targets, out);
     return hipGetLastError();
 }
 

@@ -103,6 +103,10 @@ struct GemmArgs {
 struct GemmArgsX : GemmArgs {
     float2* lse;                  // EPI_LSE: [column tiles of kLseCols][M]
     float T;                      // EPI_LSE: temperature (> 0)
+    // EPI_LSE: row m's items row_items[m] .. row_items[m + 1] of item_idx, each an index into targets and out_logp,
+    // which receives the target's logit / T (targets outside [0, Nw): nothing)
+    const int32_t *row_items, *item_idx, *targets;
+    float* out_logp;
     // grouped expert projection (launch_moe_tiles): A rows are gathered and
     // the outputs placed as launch_moe_gemv does
     const int32_t* g_off;         // [g_E + 1] ranges of pairs per expert
@@ -116,8 +120,8 @@ struct GemmArgsX : GemmArgs {
 };
 
 // Scoring head: logits are reduced to one (max, sum-exp) per row and kLseCols
-// columns inside the GEMM (launch_gemm_lse) and never written;
-// launch_logprob_lse merges them and computes each target's logit itself.
+// columns inside the GEMM (launch_gemm_lse) and never written, but for each
+// target's own; launch_logprob_lse merges the pairs and subtracts.
 constexpr int kLseCols = 256;
 
 // Mixture of experts: one grouped expert projection (k_moe.hip).
@@ -289,11 +293,10 @@ hipError_t launch_logprob(const float* logits, int ld, int n_rows, int V, const 
                           hipStream_t s);
 
 hipError_t launch_gemm_lse(const GemmArgsX& a, hipStream_t s);   // bf16, K % 64 == 0, operands under 4 GiB
-// The same values as launch_logprob from the column tiles of launch_gemm_lse
-// ([n_tiles][n_rows]): h [n_rows][H] and w [V][H] are the head's operands.
-hipError_t launch_logprob_lse(const float2* lse, int n_tiles, int n_rows, const void* h, const void* w, int H, int V,
-                              const int32_t* row_items, const int32_t* item_idx, const int32_t* targets, float T,
-                              float* out, hipStream_t s);
+// Completes launch_gemm_lse's targets: out[idx] (the target's logit / T) becomes the log-probability, with the
+// row's log-sum-exp merged from its column tiles ([n_tiles][n_rows]); NaN for targets outside [0, V).
+hipError_t launch_logprob_lse(const float2* lse, int n_tiles, int n_rows, int V, const int32_t* row_items,
+                              const int32_t* item_idx, const int32_t* targets, float* out, hipStream_t s);
 
 // SampleParts a launch over n rows of V logits writes (0: a single chunk per
 // row, no partials).

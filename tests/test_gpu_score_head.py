@@ -45,3 +45,29 @@ def test_head_in_tiles(vocab, rlens, T):
     assert np.array_equal(np.isnan(together), np.isnan(alone)) and np.isnan(alone).sum() == 2
     # fp32 sums in another order: logits of |z| < 64 and their LSE, each a few units of 2^-24 relative, over T
     np.testing.assert_allclose(together[~np.isnan(alone)], alone[~np.isnan(alone)], rtol=0, atol=64 * 2.0 ** -21)
+
+
+def test_certain_tokens_are_not_above_zero():
+    # a greedy rollout scored again: every target is its row's largest logit, far above the rest.  The log-sum-exp
+    # is never below the largest of its terms, so no log-probability is above 0 when both come from one logit.
+    shape = ModelShape(1, 256, 4, 2, 64, 512, 1032, 1e-6, 1e4, "bf16")
+    w = make_weights(shape, 3, device="cuda", init="fanin")
+    w["lm_head"] *= 64
+    n, steps = 8, 40
+    rng = np.random.default_rng(1)
+    prompts = [rng.integers(0, shape.vocab, 5 + i).astype(np.int32) for i in range(n)]
+    eng = Engine(shape, w, max_seqs=n, max_ctx=96, max_prefill_tokens=1024)
+    tok, lp = torch.empty(n, dtype=torch.int32, device="cuda"), torch.empty(n, device="cuda")
+    ids, offs = list(range(n)), np.concatenate([[0], np.cumsum([len(p) for p in prompts])])
+    eng.prefill(ids, ids, offs, torch.as_tensor(np.concatenate(prompts), device="cuda"), tok, lp, temperature=0.0)
+    out = [tok.clone()]
+    for _ in range(steps - 1):
+        eng.step(ids, ids, out[-1], tok, lp, temperature=0.0)
+        out.append(tok.clone())
+    eng.release(ids)
+    resp = list(torch.stack(out, 1).cpu().numpy())
+    together = score(eng, prompts, 1, resp, 1.0)   # 8 x 40 head rows: in tiles
+    alone = np.concatenate([score(eng, [prompts[i]], 1, [resp[i]], 1.0) for i in range(n)])
+    eng.close()
+    for lps in (together, alone):
+        assert lps.max() <= 0.0 and np.mean(lps > -1e-3) > 0.5   # most of them certain
