@@ -863,7 +863,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(
 #pragma unroll
                 for (int e = 0; e < 4; ++e) m = fmaxf(m, z[q][e]);
             m = fmaxf(m, __shfl_xor(m, 1, 64));
-            const float m_use = fabsf(m) == INFINITY ? 0.0f : m;   // no finite entry to shift by
+            const float m_use = m == -INFINITY ? 0.0f : m;   // no entry to shift by
             float s = 0.0f;
 #pragma unroll
             for (int q = 0; q < 8; ++q)
@@ -894,7 +894,9 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(
             float s = 0.0f;
 #pragma unroll
             for (int q = 0; q < WN; ++q) s += v[q].x == m ? v[q].y : v[q].y * __expf(v[q].x - m);
-            p.lse[static_cast<size_t>(n_tile) * M + m0 + row] = make_float2(m, s);
+            // a NaN logit (or a +inf one, whose row has no log-sum-exp) makes the sum NaN; the maximum skips NaN and is
+            // -inf where a whole tile is NaN, which the merge takes for an empty tile: NaN there as well
+            p.lse[static_cast<size_t>(n_tile) * M + m0 + row] = make_float2(isnan(s) ? s : m, s);
         }
         return;
     }

@@ -275,7 +275,8 @@ hipError_t launch_sample(const float* logits, int ld, int n, int V, const int32_
 
 // Inference-stage log-probabilities of given tokens, one workgroup per logits
 // row: the row's LSE of fl32(z / T) (online max / sum-exp per lane, merged in
-// a fixed lane and wave order), then every item of the row.  No noise.
+// a fixed lane and wave order), then every item of the row.  No noise.  NaN and
+// +inf logits leave a row no log-sum-exp (NaN), -inf ones add nothing to it.
 __global__ void __launch_bounds__(256) logprob_kernel(const float* __restrict__ logits, int ld, int V,
         const int32_t* __restrict__ row_items, const int32_t* __restrict__ item_idx,
         const int32_t* __restrict__ targets, float T, float* __restrict__ out) {
@@ -292,11 +293,12 @@ __global__ void __launch_bounds__(256) logprob_kernel(const float* __restrict__ 
             if (zt > acc.m) {
                 acc.s = acc.s * expf(acc.m - zt) + 1.0f;
                 acc.m = zt;
-            } else {
+            } else if (zt != -INFINITY) {
                 acc.s += expf(zt - acc.m);
             }
         }
     }
+    if (isnan(acc.s)) acc.m = acc.s;   // a lane with a NaN or +inf logit: the merge drops maxima of -inf, not this
     for (int off = 32; off > 0; off >>= 1) {
         Lse o{__shfl_xor(acc.m, off, 64), __shfl_xor(acc.s, off, 64)};
         acc = lse_merge(acc, o);

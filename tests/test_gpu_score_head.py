@@ -66,8 +66,34 @@ def test_certain_tokens_are_not_above_zero():
         out.append(tok.clone())
     eng.release(ids)
     resp = list(torch.stack(out, 1).cpu().numpy())
-    together = score(eng, prompts, 1, resp, 1.0)   # 8 x 40 head rows: in tiles
+    eng.set_option(RL_OPT_GEMM_PLAN, gemm_plan_code(RL_GEMM_T256))
+    together = score(eng, prompts, 1, resp, 1.0)   # in tiles
+    eng.set_option(RL_OPT_GEMM_PLAN, 0)
     alone = np.concatenate([score(eng, [prompts[i]], 1, [resp[i]], 1.0) for i in range(n)])
     eng.close()
     for lps in (together, alone):
         assert lps.max() <= 0.0 and np.mean(lps > -1e-3) > 0.5   # most of them certain
+
+
+# a whole column tile of the logit (and whole lanes of the other head's sum), or one of its columns
+@pytest.mark.parametrize("rows", [slice(256, 512), slice(700, 701), slice(0, 4)])
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+def test_logits_that_are_not_finite(rows, value):
+    shape = ModelShape(1, 256, 4, 2, 64, 512, 1032, 1e-6, 1e4, "bf16")
+    w = make_weights(shape, 3, device="cuda", init="fanin")
+    w["embed"].fill_(1.0), w["final_norm"].fill_(1.0), w["w_o"].zero_(), w["w_down"].zero_()   # hidden states of 1
+    w["lm_head"][rows, 0] = value
+    rng = np.random.default_rng(2)
+    prompts = [rng.integers(0, shape.vocab, 9).astype(np.int32)]
+    resp = [rng.integers(4, 200, 70).astype(np.int32) for _ in range(4)]
+    eng = Engine(shape, w, max_seqs=4, max_ctx=96, max_prefill_tokens=1024)
+    eng.set_option(RL_OPT_GEMM_PLAN, gemm_plan_code(RL_GEMM_T256))   # in tiles
+    together = score(eng, prompts, 4, resp, 0.7)
+    eng.set_option(RL_OPT_GEMM_PLAN, 0)
+    alone = score(eng, prompts, 1, resp[:1], 0.7)
+    eng.close()
+    if value == -np.inf:   # left out of the sum
+        assert np.isfinite(together).all()
+        np.testing.assert_allclose(together[:70], alone, rtol=0, atol=64 * 2.0 ** -21)
+    else:   # the row has no log-sum-exp
+        assert np.isnan(alone).all() and np.isnan(together).all()
