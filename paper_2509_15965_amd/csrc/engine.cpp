@@ -1459,7 +1459,10 @@ rl_status build_items(rl_decode_ctx* c, Meta* m, const std::vector<Block>& block
 // against 153; 131 rows of 300-1300 on pages, mixture of experts: 47 against 77).
 constexpr int kCutSnap = 16;      // 1 / 16 of a run
 constexpr double kStreamKeyBytes = 16e6;
-constexpr int kMinRunSteps = 2;   // fewer rows: a run still holds 64 keys
+// Few keys: a run still holds 64 of them, but no wave takes a second row while
+// others idle (4 rows of 2 keys, 28 q-heads over 4 kv-heads, 2 layers: 287 us a
+// step with a wave each, 290 with two rows a wave).
+constexpr int kMinRunSteps = 2;
 rl_status build_runs(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks, Fwd* f) {
     const int Hkv = c->cfg.n_kv_heads;
     auto steps_of = [](const Block& b) { return ceil_div(b.pos0 + b.nq, 32); };
@@ -1472,7 +1475,7 @@ rl_status build_runs(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks
         scorepos += b.pos0 + b.nq;
     }
     int64_t waves = std::max(1, kAttnWaveTarget / Hkv);
-    waves = std::min(waves, total / kMinRunSteps);
+    waves = std::min(waves, std::max<int64_t>(total / kMinRunSteps, static_cast<int64_t>(blocks.size())));
     waves = std::min(waves, total * (kMaxCombine - 2) / longest);   // a row is cut into at most kMaxCombine items
     waves = std::max<int64_t>(waves, 1);
     const int64_t snap = total / waves / kCutSnap;
