@@ -1305,9 +1305,30 @@ std::vector<int> place_shared(const std::vector<AttnItem>& its, const std::vecto
     return order;
 }
 
-// once: every block is the only one of its slot's own keys (decode steps), so
-// each of its items reads keys that no other item of the launch does.
-rl_status build_items(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks, int C, bool once, Fwd* f) {
+// Leading positions of a slot whose pages other slots hold as well (a group's
+// prompt in a paged pool): other rows' items may read them too.
+int shared_page_positions(const rl_decode_ctx* c, int slot) {
+    if (!c->paged()) return 0;
+    int j = 0;
+    while (j < c->npages[slot] && c->pref[c->ptab[static_cast<size_t>(slot) * c->lay.maxp + j]] > 1) ++j;
+    return j * c->lay.page;
+}
+
+// Whether a decode step that reads `keys` positions of a layer once streams
+// them past the caches (kAttnOnce): fewer displace nothing worth keeping.  With
+// full-length rows the hint is worth 4-11% of a step (512 rows of 1000 keys, 7B
+// shape, 2 layers: 997 us against 1079).
+constexpr double kStreamKeyBytes = 16e6;
+bool streams_keys(const rl_decode_ctx* c, int64_t keys) {
+    return 2.0 * keys * c->cfg.n_kv_heads * c->cfg.head_dim * c->lay.es >= kStreamKeyBytes;
+}
+
+// decode: every block is a row of its own slot, so only keys in shared pages
+// are read by more than one of the items over own keys.
+rl_status build_items(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks, int C, bool decode, Fwd* f) {
+    int64_t own = 0;
+    for (const Block& b : blocks) own += b.pos0 + b.nq - (b.src >= 0 ? b.plen : 0);
+    const bool stream = decode && streams_keys(c, own);
     std::vector<AttnItem> its;
     std::vector<int64_t> key;
     std::vector<int> split_first;
@@ -1319,6 +1340,7 @@ rl_status build_items(rl_decode_ctx* c, Meta* m, const std::vector<Block>& block
         const bool sh = b.src >= 0 && b.plen > 0;
         const int n_sh = sh ? ceil_div(b.plen, C) : 0;
         const int lo_own = sh ? b.plen : 0;
+        const int in_shared = stream ? shared_page_positions(c, b.slot) : 0;
         const int nch = n_sh + ceil_div(hi_all - lo_own, C);
         const int part0 = nch > 1 ? part : -1;
         if (nch > kMaxCombine) return fail(c, RL_ERR_CAPACITY, "too many split-KV chunks in one block");
@@ -1342,7 +1364,7 @@ rl_status build_items(rl_decode_ctx* c, Meta* m, const std::vector<Block>& block
                 it.kv_lo = lo_own + j * C;
                 it.kv_hi = std::min(hi_all, lo_own + (j + 1) * C);
                 key.push_back(-1);
-                it.flags = once ? kAttnOnce : 0;
+                it.flags = stream && it.kv_lo >= in_shared ? kAttnOnce : 0;
             }
             it.part = nch > 1 ? part++ : -1;
             it.part0 = part0;
@@ -1458,7 +1480,6 @@ rl_status build_items(rl_decode_ctx* c, Meta* m, const std::vector<Block>& block
 // remainder, where the longest item decided; 48 rows of 1000-6000, 32B: 125 us
 // against 153; 131 rows of 300-1300 on pages, mixture of experts: 47 against 77).
 constexpr int kCutSnap = 16;      // 1 / 16 of a run
-constexpr double kStreamKeyBytes = 16e6;
 // Few keys: a run still holds 64 of them, but no wave takes a second row while
 // others idle (4 rows of 2 keys, 28 q-heads over 4 kv-heads, 2 layers: 287 us a
 // step with a wave each, 290 with two rows a wave).
@@ -1479,9 +1500,7 @@ rl_status build_runs(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks
     waves = std::min(waves, total * (kMaxCombine - 2) / longest);   // a row is cut into at most kMaxCombine items
     waves = std::max<int64_t>(waves, 1);
     const int64_t snap = total / waves / kCutSnap;
-    // keys of a layer too few to displace anything keep to the caches
-    const bool large = 32.0 * total * Hkv * c->cfg.head_dim * 2 * c->lay.es >= kStreamKeyBytes;
-    const int32_t stream = large ? kAttnOnce : 0;
+    const bool stream = streams_keys(c, 32 * total);
     AttnItem* dItems = nullptr;
     const size_t cap = blocks.size() + static_cast<size_t>(waves);
     if (cap > static_cast<size_t>(c->lay.items_cap)) return fail(c, RL_ERR_CAPACITY, "too many attention work items");
@@ -1494,6 +1513,7 @@ rl_status build_runs(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks
     int64_t pos = 0, wave_end = -1;   // steps placed so far, and where the current wave's run ends
     for (const Block& b : blocks) {
         const int ns = steps_of(b), hi = b.pos0 + b.nq, n0 = n;
+        const int in_shared = stream ? shared_page_positions(c, b.slot) : 0;
         const int64_t row_end = pos + ns;
         int64_t at = pos;
         while (at < row_end) {
@@ -1511,7 +1531,7 @@ rl_status build_runs(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks
             it.kv_lo = static_cast<int>(at - pos) * 32;
             it.kv_hi = std::min<int>(hi, static_cast<int>(to - pos) * 32);
             it.part = -1; it.qrow_b = -1; it.part_b = -1;
-            it.flags = stream;
+            it.flags = stream && it.kv_lo >= in_shared ? kAttnOnce : 0;
             at = to;
             // a run that ends just past a row's end ends there
             if (at == row_end && n_waves < waves && wave_end - at <= snap) wave_end = at;

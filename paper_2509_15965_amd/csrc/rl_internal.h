@@ -83,7 +83,8 @@ struct AttnItem {
 constexpr int32_t kAttnLds = 1;    // on the first item of a workgroup whose four items read the same shared
                                    // prompt chunk (same slot and key range): the workgroup stages each
                                    // K/V step through LDS once
-constexpr int32_t kAttnOnce = 2;   // no other item of the launch reads these keys
+constexpr int32_t kAttnOnce = 2;   // no other item of the launch reads these keys, and the launch reads enough of them
+                                   // to stream past the caches: non-temporal loads
 
 struct GemmArgs {
     const void* A;   int lda;     // [M][K] model dtype
