@@ -112,7 +112,11 @@ GemmPlan plan_gemm_bf16(int M, int Nw, int K, int epi, int F) {
     const double wbytes = 2.0 * Nw * K;
     const double floor_us = wbytes / 5.2e6;
     const double out_us = (epi == EPI_F32 ? 4.0 : epi == EPI_RESID ? 8.0 : 2.0) * M * n_out / 4.0e6;
-    auto reduce_us = [&](int s) { return s > 1 ? 8.0 * s * M * static_cast<double>(Nw) / 3.0e6 + 4.0 : 0.0; };
+    // SwiGLU's slices are summed by a launch of their own (6.5 us; the others' sums run in the kernel that takes the
+    // result).  Up to 32 rows the GEMV form is underpriced by as much, and the lower figure compares right (8 rows,
+    // 7B shape, 2 layers: 310 us a step with slices, 318 with the GEMV form)
+    const double reduce_fixed = epi == EPI_SWIGLU && M > 32 ? 6.5 : 4.0;
+    auto reduce_us = [&](int s) { return s > 1 ? 8.0 * s * M * static_cast<double>(Nw) / 3.0e6 + reduce_fixed : 0.0; };
 
     GemmPlan best_p{};
     double best = 1e30;
