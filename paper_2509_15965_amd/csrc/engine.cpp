@@ -737,20 +737,19 @@ rl_status run_moe(rl_decode_ctx* c, int l, int n, const void* h) {
     int32_t* off = c->wsp<int32_t>(L.off_moe_off);
     hipError_t e;
     // row tiles of the experts, in the split-K partials (free between the router and the next projection)
-    int bm = 0;
-    const bool tiled = moe_tiles_fit(n * k, n, E, H, Fe, &bm);
+    const MoeTiles mt = moe_tiles(n * k, n, E, H, Fe);
     int32_t* toff = c->wsp<int32_t>(L.off_part);
     int32_t* tiles = toff + E + 1;
     {
         Prof pr(c, RL_K_MOE_ROUTE);
-        e = launch_moe_route(logits, n, E, k, ids, pw, off, pairs, bm, toff, tiles, c->stream);
+        e = launch_moe_route(logits, n, E, k, ids, pw, off, pairs, mt.bm, toff, tiles, c->stream);
         if (e != hipSuccess) return hip_fail(c, e, "expert routing launch");
         pr.done(n * (E * 4.0 + k * 12.0), 0.0);
     }
     MoeArgs a{};
     a.E = E; a.k = k; a.n_rows = n; a.npairs = n * k;
     a.off = off; a.pairs = pairs; a.pw = pw;
-    a.bm = bm; a.toff = toff; a.tiles = tiles;
+    a.bm = mt.bm; a.toff = toff; a.tiles = tiles;
     a.w_cached = c->w_cached;
     {
         Prof pr(c, RL_K_MOE_EXPERTS);
@@ -760,7 +759,7 @@ rl_status run_moe(rl_decode_ctx* c, int l, int n, const void* h) {
         g.w_expert = static_cast<size_t>(2) * Fe * H; g.ldw = H; g.K = H; g.Nw = 2 * Fe; g.F = Fe;
         g.groups = (Fe + kMoeRowsPerGroup / 2 - 1) / (kMoeRowsPerGroup / 2);
         g.act = reinterpret_cast<uint16_t*>(c->ws + L.off_moe_act); g.ld_act = Fe;
-        e = tiled ? launch_moe_tiles(g, EPI_SWIGLU, c->stream) : launch_moe_gemv(g, EPI_SWIGLU, c->stream);
+        e = mt.gate_up ? launch_moe_tiles(g, EPI_SWIGLU, c->stream) : launch_moe_gemv(g, EPI_SWIGLU, c->stream);
         if (e != hipSuccess) return hip_fail(c, e, "expert gate|up launch");
         MoeArgs d = a;   // down: SwiGLU rows -> weighted output planes
         d.A = g.act; d.lda = Fe;
@@ -768,7 +767,7 @@ rl_status run_moe(rl_decode_ctx* c, int l, int n, const void* h) {
         d.w_expert = static_cast<size_t>(H) * Fe; d.ldw = Fe; d.K = Fe; d.Nw = H; d.F = 0;
         d.groups = (H + kMoeRowsPerGroup - 1) / kMoeRowsPerGroup;
         d.plane = c->wsp<float>(L.off_moe_out);
-        e = tiled ? launch_moe_tiles(d, EPI_RESID, c->stream) : launch_moe_gemv(d, EPI_RESID, c->stream);
+        e = mt.down ? launch_moe_tiles(d, EPI_RESID, c->stream) : launch_moe_gemv(d, EPI_RESID, c->stream);
         if (e != hipSuccess) return hip_fail(c, e, "expert down launch");
         // bytes: the experts that can be reached (at most n * k of E) and the pairs' rows
         const double reach = std::min<double>(E, static_cast<double>(n) * k);

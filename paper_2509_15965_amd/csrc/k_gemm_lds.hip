@@ -1097,27 +1097,37 @@ hipError_t launch_tile_variant(int variant, const GemmArgs& a, const GemmPlan& p
 
 }  // namespace
 
-// The experts' projections in tiles, or in the GEMV form (launch_moe_gemv).
-// Both are bound by the stream of the experts' weights while an expert has few
-// pairs; the tiles' DMA ring streams them a little faster from 2 pairs per
-// expert on (128 experts of 768, hidden 2048, both projections: 32 rows 232 ->
-// 221 us, 131 rows 283 -> 251), and below the GEMV form's smaller workgroups
-// spread the few experts reached better (8 rows: 102 against 111).  Past 64
-// pairs the GEMV form re-reads the weights from L2 for every 64 pairs (12800
-// rows: 4627 -> 1400 us).  256-row tiles are the faster ones once they are
-// mostly full (30000 rows: 2938 -> 2685 us; 12800: 1400 -> 1437).
-constexpr int kMoeTilePairs = 2;        // mean pairs per expert from which tiles are used
-constexpr int kMoeTile256Pairs = 1024;  // and from which they hold 256 pairs
-bool moe_tiles_fit(int npairs, int n_rows, int E, int H, int Fe, int* bm) {
+// The experts' projections in tiles, or in the GEMV form (launch_moe_gemv),
+// each projection by itself.  Both are bound by the stream of the experts'
+// weights while an expert has few pairs.  The tiles' DMA ring streams them
+// faster from 2 pairs per expert on where there are enough tiles: 128 experts
+// of 768, hidden 2048, 32 rows, both projections 230 -> 194 us; 64 of 1408, 24
+// rows, 211 -> 184; and 256 gate|up tiles of K 2048 (8 of 4096, hidden 2048, 16
+// rows) 12 us faster of 93, but 256 of K 4096 (16 of 2048, hidden 4096) 8 us
+// slower of 166, as are 256 down tiles of K 2048 (same model) 4 us.  With fewer
+// the GEMV form's smaller workgroups spread over more CUs, until its
+// activations, read again for every 64 weight rows, cost as much: 128 down
+// tiles (8 of 14336, hidden 4096) 8 us slower of 517 at 2 pairs, even at 8, 16
+// faster of 604 at 16; 256 gate|up tiles of K 4096 4 us slower of 172 at 8, 5
+// faster of 178 at 12; 64 and 16 tiles (8 of 4096, hidden 2048, down; 4 of 1024,
+// hidden 1024) 18 and 6 us slower of 93 and 22 at 4, 16 and 5 faster of 180 and
+// 46 at 64.  Past 64 pairs the GEMV form also re-reads the weights from L2 for
+// every 64 (12800 rows: 4627 -> 1400 us).  256-row tiles are the faster ones
+// once they are mostly full (30000 rows: 2938 -> 2685 us; 12800: 1400 -> 1437).
+constexpr int kMoeTile256Pairs = 1024;  // mean pairs per expert from which tiles hold 256
+MoeTiles moe_tiles(int npairs, int n_rows, int E, int H, int Fe) {
     constexpr uint64_t kOffLimit = 0xFFFFFFFFull;
-    if (H % 64 != 0 || Fe % 64 != 0) return false;
+    MoeTiles t{0, false, false};
+    if (H % 64 != 0 || Fe % 64 != 0) return t;
     if (static_cast<uint64_t>(n_rows) * H * 2 > kOffLimit || static_cast<uint64_t>(npairs) * Fe * 2 > kOffLimit ||
         static_cast<uint64_t>(2) * Fe * H * 2 > kOffLimit)
-        return false;
+        return t;
     const int avg = npairs / E;
-    if (avg < kMoeTilePairs) return false;
-    *bm = avg < kMoeTile256Pairs ? 128 : 256;
-    return true;
+    const int gu = E * ((Fe + 127) / 128), dn = E * ((H + 255) / 256);   // tiles at one row tile per expert
+    t.gate_up = avg >= 64 || (avg >= 12 && gu >= 128) || (avg >= 2 && (gu >= 384 || (gu >= 256 && H <= 2048)));
+    t.down = avg >= 64 || (avg >= 8 && dn >= 128) || (avg >= 2 && dn >= 384);
+    if (t.gate_up || t.down) t.bm = avg < kMoeTile256Pairs ? 128 : 256;
+    return t;
 }
 
 hipError_t launch_moe_tiles(const MoeArgs& a, int epi, hipStream_t s) {

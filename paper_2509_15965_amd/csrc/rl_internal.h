@@ -239,7 +239,9 @@ hipError_t launch_moe_route(const float* logits, int n, int E, int k, int32_t* i
 // The same projection as launch_moe_gemv in MFMA tiles of bm pairs x 256 weight
 // rows (K a multiple of 64; activations and one expert's weights under 4 GiB).
 hipError_t launch_moe_tiles(const MoeArgs& a, int epi, hipStream_t s);
-bool moe_tiles_fit(int npairs, int n_rows, int E, int H, int Fe, int* bm);   // whether, and with which bm, a layer takes them
+// Which projections of a layer take them, and with which bm (0: neither).
+struct MoeTiles { int bm; bool gate_up, down; };
+MoeTiles moe_tiles(int npairs, int n_rows, int E, int H, int Fe);
 // One grouped expert projection (epi: EPI_SWIGLU for gate|up, EPI_RESID for
 // down, which writes routing-weighted planes).
 hipError_t launch_moe_gemv(const MoeArgs& a, int epi, hipStream_t s);

@@ -13,9 +13,11 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 
-# pairs per expert = rows.  1 row: the GEMV form; 1100 and 1024: tiles of 256
+# pairs per expert = rows.  1 row, and 2 rows of 8 narrow experts: the GEMV form; 1100 and 1024: tiles of 256.  16
+# experts of 2048 at hidden 128: gate|up alone in tiles (256) from 2 rows; at hidden 4096 and 8 rows: down alone
 @pytest.mark.parametrize("E,rows,hidden,ffn", [(8, 1, 128, 64), (8, 2, 128, 64), (3, 128, 192, 192), (4, 129, 320, 64),
-                                               (4, 600, 128, 320), (2, 1100, 128, 64), (2, 1024, 192, 192)])
+                                               (4, 600, 128, 320), (2, 1100, 128, 64), (2, 1024, 192, 192),
+                                               (4, 63, 128, 64), (4, 64, 128, 64), (16, 8, 4096, 64), (16, 2, 128, 2048)])
 def test_expert_tiles(E, rows, hidden, ffn):
     shape = ModelShape(1, hidden, 2, 1, 64, 0, 264, 1e-6, 1e4, "bf16", n_experts=E, top_k=E, expert_ffn=ffn)
     w, _, om = build_models(shape, 11, init="fanin")
