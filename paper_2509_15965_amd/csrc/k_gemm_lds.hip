@@ -864,6 +864,10 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(
                 for (int e = 0; e < 4; ++e) m = fmaxf(m, z[q][e]);
             m = fmaxf(m, __shfl_xor(m, 1, 64));
             const float m_use = m == -INFINITY ? 0.0f : m;   // no entry to shift by
+            // the hardware's exponential: the rounding of x log2(e) grows with -x as the term shrinks.  Against 64 bits, on
+            // logits that are exact in every kernel (vocab 264 - 152064, spread 0.5 - 8): 3.1e-7 - 2.1e-6 rms of a
+            // log-probability; with expf the same, and 3.0e-7 - 2.2e-6 in the other head, which sums more terms one
+            // after the other.  expf here costs 3 - 12% of the head.
             float s = 0.0f;
 #pragma unroll
             for (int q = 0; q < 8; ++q)

@@ -97,3 +97,29 @@ def test_logits_that_are_not_finite(rows, value):
         np.testing.assert_allclose(together[:70], alone, rtol=0, atol=64 * 2.0 ** -21)
     else:   # the row has no log-sum-exp
         assert np.isnan(alone).all() and np.isnan(together).all()
+
+
+@pytest.mark.parametrize("vocab,spread", [(264, 4.0), (4096, 1.0), (32000, 2.0)])
+def test_error_against_64_bits(vocab, spread):
+    # logits that are exact in every kernel (hidden states of 1, one weight a row), so that the sums alone differ: the
+    # head in tiles is no further from 64 bits than the one over written logits
+    s = ModelShape(1, 64, 1, 1, 64, 64, vocab, 1e-6, 1e4, "bf16")
+    w = make_weights(s, 3, device="cuda", init="fanin")
+    w["embed"].fill_(1.0), w["final_norm"].fill_(1.0), w["w_o"].zero_(), w["w_down"].zero_(), w["lm_head"].zero_()
+    eng = Engine(s, w, max_seqs=2, max_ctx=96, max_prefill_tokens=512)
+    err = {RL_GEMM_T256: [], RL_GEMM_T128: []}
+    for seed in range(8):
+        z = torch.randn(vocab, generator=torch.Generator("cuda").manual_seed(seed), device="cuda") * spread
+        w["lm_head"][:, 0] = z.bfloat16()
+        zz = w["lm_head"][:, 0].float()
+        resp = [np.array([int(zz.argmax())] + list(range(69)), np.int32)] * 2
+        for T in (1.0, 0.6, 0.83):
+            zt = (zz / np.float32(T)).double()
+            ref = (zt[torch.as_tensor(np.concatenate(resp), device="cuda").long()] - torch.logsumexp(zt, 0)).cpu().numpy()
+            for plan in err:
+                eng.set_option(RL_OPT_GEMM_PLAN, gemm_plan_code(plan))
+                err[plan].append(score(eng, [resp[0][:1]], 2, resp, T) - ref)
+    eng.close()
+    tiles, logits = (np.sqrt(np.mean(np.square(np.array(err[p], dtype=np.float64)))) for p in err)
+    # both are mostly the final roundings (half an ulp of values up to 40: 1.9e-6); rms over 24 sums, so a fifth apart at most
+    assert tiles < 1.2 * logits and tiles < 1.9e-6
