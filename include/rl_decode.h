@@ -267,10 +267,15 @@ rl_status rl_prefill(rl_decode_ctx* ctx, int32_t n_prompts, int32_t group,
  *                 prompt and response tokens 0..j-1; NaN when y is outside
  *                 [0, vocab).
  * The slots serve as scratch: their K/V is overwritten and they are empty
- * (length 0) afterwards.  In bf16 more than 128 LM-head rows are reduced to
- * their log-sum-exp inside the head's GEMM; fewer go through chunks of rows
+ * (length 0) afterwards.  LM-head rows (one for each prompt's end and each
+ * response token but the last of its response) go through chunks of rows
  * whose fp32 logits fit the workspace (max_seqs rows, or more when the MLP
- * activation buffer, free by then, holds more). */
+ * activation buffer, free by then, holds more).  In bf16 with hidden a
+ * multiple of 64, more than 128 rows are instead reduced to their log-sum-exp
+ * inside the head's GEMM where the vocabulary is large enough for that to be
+ * the faster way; RL_OPT_GEMM_PLAN = RL_GEMM_T256 does so at every size, any
+ * other override at none.  A token's log-probability is never above 0; a row
+ * with a NaN or +inf logit leaves NaN. */
 rl_status rl_score(rl_decode_ctx* ctx, int32_t n_prompts, int32_t group, const int32_t* slots,
                    const int32_t* prompt_offsets, const int32_t* prompt_tokens,
                    const void* embeds, int32_t n_embed_rows,

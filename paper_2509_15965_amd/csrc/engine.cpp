@@ -777,14 +777,25 @@ rl_status run_moe(rl_decode_ctx* c, int l, int n, const void* h) {
     return RL_OK;
 }
 
-// Scoring passes of more LM-head rows than this reduce the logits inside the
-// head's 256 x 256 tiles; fewer go through the decode kernels and a logits buffer.
+// Scoring passes of more than 128 LM-head rows reduce the logits inside the
+// head's 256 x 256 tiles where these fill about half the chip, or where the
+// logits buffer takes the rows in several chunks; others go through the decode
+// kernels and the buffer.  Head and log-probabilities, logits against tiles:
+// K 3584, 96 tiles 70 and 80 us, 128 tiles 87 and 83, 256 tiles 137 and 123, 2000
+// tiles 941 and 806; K 5120, 125 and 126 tiles 124 and 121, 100 and 110; K 1536, 94
+// tiles 46 and 47, 126 tiles 50 and 49; K 256, 30 tiles 24 and 27, 48 tiles 26 and
+// 25; in 4 chunks of 64 rows, K 3584, 16 tiles 91 and 79.
 // An override decides by its kernel, whatever the row count: with one kernel for
 // every size, a sequence's scores do not depend on what is scored beside it.
 constexpr int kFusedHeadRows = 128;
-bool fused_head(const rl_decode_ctx* c, int rows) {
-    if (!c->bf16() || c->cfg.hidden % 64 != 0) return false;
-    return c->opt_gemm == 0 ? rows > kFusedHeadRows : c->opt_gemm == RL_GEMM_T256;
+bool fused_head(const rl_decode_ctx* c, int rows, int chunk) {
+    const int K = c->cfg.hidden;
+    if (!c->bf16() || K % 64 != 0) return false;
+    if (c->opt_gemm != 0) return c->opt_gemm == RL_GEMM_T256;
+    if (rows <= kFusedHeadRows) return false;
+    const int64_t tiles = static_cast<int64_t>(ceil_div(rows, 256)) * ceil_div(c->cfg.vocab, kLseCols);
+    const int chunks = ceil_div(rows, chunk);
+    return tiles >= std::min(120, 24 + K / 16) || (chunks > 1 && chunks * 1024 >= K);
 }
 
 rl_status run_forward(rl_decode_ctx* c, const Fwd& f) {
@@ -901,7 +912,7 @@ rl_status run_forward(rl_decode_ctx* c, const Fwd& f) {
         if (e != hipSuccess) return hip_fail(c, e, "final rmsnorm launch");
         pr.done(nf * H * (4.0 + es) + H * es, 0.0);
     }
-    if (f.score_items && fused_head(c, nf)) {
+    if (f.score_items && fused_head(c, nf, f.score_chunk)) {
         // rows whose column tiles (one float2 per row and kLseCols logits) fit the split-K partials
         const int V = cf.vocab, n_tiles = ceil_div(V, kLseCols);
         const size_t fit = L.part_floats / 2 / n_tiles;

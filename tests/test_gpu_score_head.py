@@ -1,12 +1,14 @@
-"""The scoring head that reduces logits inside its GEMM tiles (more than 128 head rows) against the one that
-writes them (each sequence scored alone), on the same hidden states."""
+"""The scoring head that reduces logits inside its GEMM tiles against the one that writes them (each sequence scored
+alone), on the same hidden states."""
 import numpy as np
 import pytest
 import torch
 
+from harness import LOGP_ABS_TOL
 from paper_2509_15965_amd.configs import ModelShape
 from paper_2509_15965_amd.inputs import make_weights
-from paper_2509_15965_amd.rl_decode import RL_GEMM_T128, RL_GEMM_T256, RL_OPT_GEMM_PLAN, Engine, gemm_plan_code
+from paper_2509_15965_amd.rl_decode import (KERNEL_CLASSES, RL_GEMM_T128, RL_GEMM_T256, RL_OPT_GEMM_PLAN, RL_OPT_PROFILE,
+                                            Engine, gemm_plan_code)
 
 pytestmark = pytest.mark.gpu
 
@@ -21,7 +23,7 @@ def score(eng, prompts, group, resp, T):
     return out.cpu().numpy()
 
 
-# head rows 129 (just past the line), 256 (a whole row tile), 257 and 600; vocabularies of one ragged column tile, whole
+# head rows 130, 256 (a whole row tile), 257 and 585, in tiles by override; vocabularies of one ragged column tile, whole
 # tiles and a ragged last one
 @pytest.mark.parametrize("vocab,rlens,T", [(200, [65, 65, 1, 1], 1.0), (512, [64, 64, 64, 66], 0.6), (1032, [64, 64, 64, 67], 0.0),
                                            (1288, [100, 120, 40, 90, 110, 128], 0.6)])
@@ -123,3 +125,27 @@ def test_error_against_64_bits(vocab, spread):
     tiles, logits = (np.sqrt(np.mean(np.square(np.array(err[p], dtype=np.float64)))) for p in err)
     # both are mostly the final roundings (half an ulp of values up to 40: 1.9e-6); rms over 24 sums, so a fifth apart at most
     assert tiles < 1.2 * logits and tiles < 1.9e-6
+
+
+# the default choice: 128 head rows over written logits, 129 in tiles where the vocabulary has enough of them (41 column
+# tiles at hidden 256, and not 39) or where the logits buffer takes the rows in more than one chunk
+@pytest.mark.parametrize("vocab,rlens,ffn,tiles", [(10248, [65, 64], 512, False), (10248, [65, 65], 512, True),
+                                                   (9800, [65, 65], 512, False), (9800, [65, 65], 64, True)])
+def test_default_choice(vocab, rlens, ffn, tiles):
+    shape = ModelShape(1, 256, 4, 2, 64, ffn, vocab, 1e-6, 1e4, "bf16")
+    w = make_weights(shape, 9, device="cuda", init="fanin")
+    rng = np.random.default_rng(vocab)
+    prompt = [rng.integers(0, vocab, 9).astype(np.int32)]
+    resp = [rng.integers(0, vocab, m).astype(np.int32) for m in rlens]
+    rows = 1 + sum(rlens) - 2
+    # max_prefill_tokens sets the MLP buffer: 8192 * 512 / (2 * vocab) rows of logits, or 8192 * 64 / (2 * vocab)
+    eng = Engine(shape, w, max_seqs=2, max_ctx=160, max_prefill_tokens=8192)
+    eng.set_option(RL_OPT_PROFILE, 1 << KERNEL_CLASSES.index("gemm_lm_head"))
+    together = score(eng, prompt, 2, resp, 1.0)
+    st = eng.kernel_stats()["gemm_lm_head"]
+    alone = np.concatenate([score(eng, prompt, 1, [r], 1.0) for r in resp])
+    eng.close()
+    logits_bytes = 4 * rows * vocab
+    assert (st["alg_bytes"] - 2 * 256 * (vocab + rows) < logits_bytes / 2) == tiles
+    # the projections' plans differ with the row count: bf16 roundings of one layer
+    assert np.abs(together - alone).max() < LOGP_ABS_TOL
