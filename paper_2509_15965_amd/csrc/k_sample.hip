@@ -13,6 +13,7 @@
 #include "rl_device.h"
 #include "rl_internal.h"
 
+#include <cfloat>
 #include <mutex>
 #include <vector>
 
@@ -283,7 +284,8 @@ __global__ void __launch_bounds__(256) logprob_kernel(const float* __restrict__ 
     __shared__ Lse sl[4];
     const int r = blockIdx.x;
     const float* z = logits + static_cast<size_t>(r) * ld;
-    Lse acc{-INFINITY, 0.0f};
+    // not -inf: a logit of -inf then adds 0, and the merge drops no lane that holds a NaN
+    Lse acc{-FLT_MAX, 0.0f};
     for (int v4 = threadIdx.x; 4 * v4 < V; v4 += blockDim.x) {
         const float4 zz = *reinterpret_cast<const float4*>(z + 4 * static_cast<size_t>(v4));
         const float zv[4] = {zz.x / T, zz.y / T, zz.z / T, zz.w / T};
@@ -293,12 +295,11 @@ __global__ void __launch_bounds__(256) logprob_kernel(const float* __restrict__ 
             if (zt > acc.m) {
                 acc.s = acc.s * expf(acc.m - zt) + 1.0f;
                 acc.m = zt;
-            } else if (zt != -INFINITY) {
+            } else {
                 acc.s += expf(zt - acc.m);
             }
         }
     }
-    if (isnan(acc.s)) acc.m = acc.s;   // a lane with a NaN or +inf logit: the merge drops maxima of -inf, not this
     for (int off = 32; off > 0; off >>= 1) {
         Lse o{__shfl_xor(acc.m, off, 64), __shfl_xor(acc.s, off, 64)};
         acc = lse_merge(acc, o);
