@@ -545,7 +545,7 @@ struct Fwd {
     int n_waves = 0;
     int n_partial_items = 0;
     const PrefillTile* tiles = nullptr;     // prefill / scoring: shared-LDS tiles instead of items
-    int n_tiles = 0;
+    int n_tiles = 0, tile_waves = 8;
     const int32_t* split_blocks = nullptr;   // first item of every split block
     int n_split_blocks = 0;
     // decode attention plan (build_items): work items, those over a shared
@@ -859,7 +859,7 @@ rl_status run_forward(rl_decode_ctx* c, const Fwd& f) {
         {
             Prof pr(c, RL_K_ATTENTION, c->bf16() && !f.tiles);
             if (c->bf16() && f.tiles)
-                e = launch_attention_prefill(f.tiles, f.n_tiles, q, c->kslab(), c->vslab(), f.kvp, Hq, Hkv, D,
+                e = launch_attention_prefill(f.tiles, f.n_tiles, f.tile_waves, q, c->kslab(), c->vslab(), f.kvp, Hq, Hkv, D,
                                              l, attn, c->stream);
             else if (c->bf16())
                 e = launch_attention_bf16(f.items, f.wave_first, f.n_waves, q, c->kslab(), c->vslab(), f.kvp, Hq, Hkv,
@@ -1576,23 +1576,30 @@ rl_status build_runs(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks
 
 // Prefill / scoring tiles: each block run of consecutive query tokens of one
 // sequence (blocks of one slot with consecutive rows and positions) split
-// into tiles of prefill_waves(G) * (32 / G) tokens, longest key range first.
+// into tiles of f->tile_waves * (32 / G) tokens, longest key range first.
 rl_status build_tiles(rl_decode_ctx* c, Meta* m, const std::vector<Block>& blocks, Fwd* f) {
     const int G = c->cfg.n_q_heads / c->cfg.n_kv_heads;
-    const int T = prefill_waves(G) * (32 / G);
+    // runs: consecutive blocks continuing the same sequence segment
+    std::vector<std::pair<size_t, int>> runs;   // first block, tokens
+    for (size_t i = 0, j; i < blocks.size(); i = j) {
+        for (j = i + 1; j < blocks.size() && blocks[j].slot == blocks[i].slot &&
+                        blocks[j].qrow == blocks[j - 1].qrow + blocks[j - 1].nq &&
+                        blocks[j].pos0 == blocks[j - 1].pos0 + blocks[j - 1].nq; ++j) {
+        }
+        runs.emplace_back(i, blocks[j - 1].qrow + blocks[j - 1].nq - blocks[i].qrow);
+    }
+    auto count = [&](int waves) {
+        int64_t n = 0;
+        for (const auto& r : runs) n += ceil_div(r.second, waves * (32 / G));
+        return n;
+    };
+    int waves = prefill_waves(G, count(8) * c->cfg.n_kv_heads);
+    const int T = waves * (32 / G);
     std::vector<PrefillTile> tl;
-    size_t i = 0;
-    while (i < blocks.size()) {
-        // a run: consecutive blocks continuing the same sequence segment
-        size_t j = i + 1;
-        while (j < blocks.size() && blocks[j].slot == blocks[i].slot &&
-               blocks[j].qrow == blocks[j - 1].qrow + blocks[j - 1].nq &&
-               blocks[j].pos0 == blocks[j - 1].pos0 + blocks[j - 1].nq)
-            ++j;
-        const int qrow0 = blocks[i].qrow, pos0 = blocks[i].pos0, slot = blocks[i].slot;
-        const int n = blocks[j - 1].qrow + blocks[j - 1].nq - qrow0;
-        for (int t = 0; t < n; t += T) tl.push_back(PrefillTile{qrow0 + t, std::min(T, n - t), slot, pos0 + t});
-        i = j;
+    for (const auto& r : runs) {
+        const Block& b = blocks[r.first];
+        for (int t = 0; t < r.second; t += T)
+            tl.push_back(PrefillTile{b.qrow + t, std::min(T, r.second - t), b.slot, b.pos0 + t});
     }
     std::stable_sort(tl.begin(), tl.end(), [](const PrefillTile& a, const PrefillTile& b) {
         return a.pos0 + a.ntok > b.pos0 + b.ntok;
@@ -1606,6 +1613,7 @@ rl_status build_tiles(rl_decode_ctx* c, Meta* m, const std::vector<Block>& block
         for (int t = 0; t < b.nq; ++t) scorepos += b.pos0 + t + 1;
     f->tiles = d;
     f->n_tiles = static_cast<int>(tl.size());
+    f->tile_waves = waves;
     f->n_waves = 0;
     f->n_split_blocks = 0;
     f->attn_score_positions = scorepos;

@@ -536,12 +536,11 @@ __global__ void __launch_bounds__(64 * WAVES) attn_prefill_kernel(const PrefillT
                            pack_bf16(o[i][4 * w + 2] * inv, o[i][4 * w + 3] * inv));
 }
 
-hipError_t launch_attention_prefill(const PrefillTile* tiles, int n_tiles, const void* q, const void* kc,
+hipError_t launch_attention_prefill(const PrefillTile* tiles, int n_tiles, int waves, const void* q, const void* kc,
                                     const void* vc, const KvPages& kp, int Hq, int Hkv, int D, int layer,
                                     void* out, hipStream_t s) {
     if (n_tiles <= 0) return hipSuccess;
     const float scale_log2 = 1.4426950408889634f / sqrtf(static_cast<float>(D));
-    const int waves = prefill_waves(Hq / Hkv);
     const dim3 grid(n_tiles, Hkv), block(64 * waves);
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, grid, block, 0, s, tiles, static_cast<const uint16_t*>(q),
@@ -550,8 +549,10 @@ hipError_t launch_attention_prefill(const PrefillTile* tiles, int n_tiles, const
     };
     if (waves == 4) {
         if (D == 128) go(attn_prefill_kernel<128, 4>); else go(attn_prefill_kernel<64, 4>);
-    } else {
+    } else if (waves == 8) {
         if (D == 128) go(attn_prefill_kernel<128, 8>); else go(attn_prefill_kernel<64, 8>);
+    } else {
+        return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

@@ -253,7 +253,7 @@ constexpr int kMaxCombine = 64;
 hipError_t launch_attn_combine(const int32_t* blocks, int n_blocks, const AttnItem* items, const float* part,
                                int Hq, int Hkv, int D, void* out, hipStream_t s);
 
-// Prefill / scoring attention tile: up to prefill_waves(G) * (32 / G) consecutive
+// Prefill / scoring attention tile: up to prefill_waves * (32 / G) consecutive
 // query tokens of one sequence (workspace rows qrow0 .., positions pos0 ..)
 // against every key they see, [0, pos0 + ntok), of one KV slot.
 struct PrefillTile {
@@ -262,17 +262,22 @@ struct PrefillTile {
     int32_t slot;
     int32_t pos0;
 };
-// Waves of a tile's workgroup.  Eight share a K/V step where a wave holds few
-// tokens; with one or two q-heads per kv-head eight waves are 128 - 256 tokens,
-// more than short prompts fill (32 prompts of 288 tokens, one q-head per
-// kv-head: 125 us with four, 151 with eight; 20.8k rows of a seven-head group:
-// 1081 and 1057).
-inline int prefill_waves(int G) { return G <= 2 ? 4 : 8; }
+// Waves of a tile's workgroup (wgs8: workgroups if they had eight).  Eight share
+// a K/V step where a wave holds few tokens; with one or two q-heads per kv-head
+// eight waves are 128 - 256 tokens, more than short prompts fill (32 prompts of
+// 288 tokens, one q-head per kv-head: 119 us with four, 151 with eight).  Where
+// eight-wave workgroups leave CUs idle, two waves on a SIMD only slow each
+// other: 1000 tokens of a seven-head group, 128 workgroups, 55 us with four
+// waves and 64 with eight; 129 tokens in 4 prompts of a six-head group 8.7 and
+// 10.8 (8.0 with 16-column tiles).  At 224 and 256 workgroups, one round of them,
+// eight are ahead: 29 and 26 us (4 prompts of 300, five-head group), 31 and 27
+// (16 of 300, six-head group).
+inline int prefill_waves(int G, int64_t wgs8) { return G <= 2 || wgs8 < 224 ? 4 : 8; }
 
 // One workgroup per (tile, kv-head): each 32-position K/V step is loaded once
 // into LDS and used by every wave (wave w takes the tile's tokens
 // [w * 32/G, (w+1) * 32/G)); outputs are final (no split partials).
-hipError_t launch_attention_prefill(const PrefillTile* tiles, int n_tiles, const void* q, const void* kc,
+hipError_t launch_attention_prefill(const PrefillTile* tiles, int n_tiles, int waves, const void* q, const void* kc,
                                     const void* vc, const KvPages& kp, int Hq, int Hkv, int D, int layer,
                                     void* out, hipStream_t s);
 

@@ -19,6 +19,19 @@ F32_LOGIT_REL_TOL = 1e-4
 F32_LOGP_ABS_TOL = 1e-4
 NEAR_TIE = 1e-4
 
+# Two bf16 versions of attention_alone's model differ by the roundings of the attention output and of the final norm,
+# each half an ulp (2^-9 of the element at most) where they flip: 2 * 2^-9 * sqrt(2) of a row's norm if all did
+ATTENTION_REL_TOL = 2.0 ** -7.5
+
+
+def attention_alone(w):
+    """Weights whose logits are the last layer's attention output and next to nothing else: embeddings (whose
+    normalised rows are as they were) at 1/128, the output projection at 128, no MLP."""
+    w["embed"] /= 128
+    w["w_o"] *= 128
+    w["w_down"].zero_()
+    return w
+
 
 def oracle_mode(shape: ModelShape) -> int:
     return oracle.MODE_BF16 if shape.dtype == "bf16" else oracle.MODE_FP32

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+from harness import ATTENTION_REL_TOL, attention_alone
 from paper_2509_15965_amd.configs import ModelShape
 from paper_2509_15965_amd.inputs import make_weights
 from paper_2509_15965_amd.rl_decode import RL_OPT_PREFILL_ATTENTION, Engine
@@ -11,14 +12,22 @@ from paper_2509_15965_amd.rl_decode import RL_OPT_PREFILL_ATTENTION, Engine
 pytestmark = pytest.mark.gpu
 
 
-# (q-heads per kv-head, head_dim); tokens per wave 32, 16, 10, 6, 4, 2 in tiles of 4 (up to two q-heads) or 8 waves
+# (q-heads per kv-head, head_dim); tokens per wave 32, 16, 10, 6, 4, 2 in tiles of 4 waves, or of 8 where these make
+# 224 workgroups (never with up to two q-heads)
+@pytest.mark.parametrize("many", [False, True])
 @pytest.mark.parametrize("G,d,page", [(1, 64, 0), (1, 128, 64), (2, 128, 0), (3, 64, 32), (5, 128, 0), (7, 128, 96), (16, 64, 0)])
-def test_tiles(G, d, page):
+def test_tiles(G, d, page, many):
     s = ModelShape(1, 256, 2 * G, 2, d, 128, 264, 1e-6, 1e4, "bf16")
-    w = make_weights(s, 6, device="cuda", init="fanin")
+    w = attention_alone(make_weights(s, 6, device="cuda", init="fanin"))
     per_wave = 32 // G
-    tile = per_wave * (4 if G <= 2 else 8)
+    tile = per_wave * (8 if many and G > 2 else 4)
     lens = [1, 2, 31, 32, 33, per_wave, per_wave + 1, tile - 1, tile, tile + 1, 2 * tile + 3]
+
+    def workgroups():   # if they had eight waves
+        return 2 * sum(-(-m // (8 * per_wave)) for m in lens)
+    while many and workgroups() < 224:
+        lens = lens + lens[:11]
+    assert many or workgroups() < 224
     n, rows = len(lens), sum(lens)
     offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     toks = torch.randint(0, s.vocab, (rows,), device="cuda", dtype=torch.int32, generator=torch.Generator("cuda").manual_seed(1))
@@ -42,9 +51,9 @@ def test_tiles(G, d, page):
     eng.close()
     (za, la), (zb, lb) = out
     assert torch.isfinite(zb).all() and torch.isfinite(lb).all()
-    # fp32 sums in another order flip bf16 roundings (2^-8 of an element): about 1e-3 of a row's norm in one layer
-    assert float(((zb - za).norm(dim=1) / za.norm(dim=1)).max()) < 1e-2
-    assert float((lb - la).abs().max()) < 2e-2
+    # one key of 260 left out moves a row by 0.06 of its norm; logits of about 1, up to 4 of them apart by their bound
+    assert float(((zb - za).norm(dim=1) / za.norm(dim=1)).max()) < ATTENTION_REL_TOL
+    assert float((lb - la).abs().max()) < 4 * ATTENTION_REL_TOL
 
 
 def offsets(lens):
