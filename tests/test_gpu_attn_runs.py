@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+from harness import ATTENTION_REL_TOL, attention_alone
 from paper_2509_15965_amd.configs import ModelShape
 from paper_2509_15965_amd.inputs import make_weights
 from paper_2509_15965_amd.rl_decode import RL_OPT_ATTN_CHUNK, Engine
@@ -23,7 +24,7 @@ SHAPES = {"g7": ModelShape(1, 448, 14, 2, 64, 128, 264, 1e-6, 1e4, "bf16"),
 def test_runs(shape, lens, page):
     s = SHAPES[shape]
     n = len(lens)
-    w = make_weights(s, 4, device="cuda", init="fanin")
+    w = attention_alone(make_weights(s, 4, device="cuda", init="fanin"))
     eng = Engine(s, w, max_seqs=n, max_ctx=max(lens) + 2, max_prefill_tokens=64, kv_page_size=page)
     slots = list(range(n))
     if page:
@@ -41,7 +42,6 @@ def test_runs(shape, lens, page):
         out.append(z.double())
     eng.close()
     assert torch.isfinite(out[1]).all()
-    # the keys' fp32 sums in another order flip bf16 roundings of the attention output and of the layers after it:
-    # two bf16 versions of one layer differ by about 1e-3 of a row's norm
+    # a 32-key step left out (or taken twice) moves a row by 0.07 of its norm at 6000 keys, one key by 0.013
     err = (out[1] - out[0]).norm(dim=1) / out[0].norm(dim=1)
-    assert float(err.max()) < 1e-2
+    assert float(err.max()) < ATTENTION_REL_TOL
