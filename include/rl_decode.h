@@ -473,8 +473,12 @@ typedef enum rl_gemm_kernel {
     RL_GEMM_T128X256 = 4,    /* 128 x 256 tiles, 8 waves                      */
     RL_GEMM_T128 = 5,        /* 128 x 128 tiles, 4 waves, two per CU          */
     RL_GEMM_T128_DEEP = 6,   /* 128 x 128 tiles, 4 waves, 4-stage ring        */
-    RL_GEMM_GEMV_WIDE = 7    /* 64 weight rows x a K slice per workgroup
+    RL_GEMM_GEMV_WIDE = 7,   /* 64 weight rows x a K slice per workgroup
                                 (M <= 64; split-K allowed)                    */
+    RL_GEMM_T256_CUT = 9     /* RL_GEMM_T256, the tiles past whole rounds of
+                                one per CU cut in K (the plain tiles where
+                                there are none to cut); no s, no second
+                                segment                                       */
 } rl_gemm_kernel;
 
 rl_status rl_decode_set_option(rl_decode_ctx* ctx, int32_t option, int64_t value);

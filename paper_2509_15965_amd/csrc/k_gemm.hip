@@ -55,9 +55,9 @@ long tiles_of(const TileKernel& t, int M, int n_cols, int epi) {
 
 // A tile grid of 256 x 256 tiles past its whole rounds leaves `rem` tiles for a
 // last round that would keep 256 - rem CUs idle; cut in K, up to 256 / rem
-// slices each, they fill it for 1 / splits of the time.  A slice keeps at
-// least 256 of K (four pipeline stages), and all partial tiles together (at
-// most 256) fit the split-K partials.
+// slices each, they fill it for 1 / splits of the time.  Slices are whole 64s
+// of at least 256 (four pipeline stages), the last one of what is left of K (64
+// or more); all partial tiles together (at most 256) fit the split-K partials.
 RemainderCut remainder_cut(int tiles, int K) {
     RemainderCut c{0, 1, K};
     const int rem = tiles % kCUs;
@@ -320,7 +320,7 @@ int64_t gemm_plan_code_of(const GemmPlan& p) {
     auto code = [](int v) -> int64_t {
         switch (v) {
             case kLineVariant256x256: return RL_GEMM_T256;
-            case kLineVariant256x256Cut: return RL_GEMM_T256;   // the same tiles, the last of them cut in K
+            case kLineVariant256x256Cut: return RL_GEMM_T256_CUT;
             case kLineVariant128x256: return RL_GEMM_T128X256;
             case kLineVariant128x128: return RL_GEMM_T128;
             case kLineVariant128x128Deep: return RL_GEMM_T128_DEEP;
@@ -346,6 +346,7 @@ bool plan_gemm_forced(int M, int Nw, int K, int epi, int F, int64_t code, GemmPl
             case RL_GEMM_T128X256: return kLineVariant128x256;
             case RL_GEMM_T128: return kLineVariant128x128;
             case RL_GEMM_T128_DEEP: return kLineVariant128x128Deep;
+            case RL_GEMM_T256_CUT: return kLineVariant256x256Cut;
             default: return -1;
         }
     };
@@ -387,6 +388,7 @@ bool plan_gemm_forced(int M, int Nw, int K, int epi, int F, int64_t code, GemmPl
     }
     const int v1 = tile(k1);
     if (v1 < 0 || K % 64 != 0) return false;
+    if (v1 == kLineVariant256x256Cut && (s > 1 || k2 != 0)) return false;
     p.variant = v1;
     p.splits = 1;
     p.ksplit = K;
