@@ -13,8 +13,10 @@
 // positions t0 + 8q .. t0 + 8q + 7; those eight probabilities are exactly
 // the lane's B operand of the P.V product, and the matching A operand is one
 // 16-byte load from the V cache's 8-position blocks.  No LDS, no transposes.
-// Online softmax in the exp2 domain, fp32 state; the probabilities enter the
-// P.V MFMA as a bf16 hi/lo pair, so they are not rounded to bf16.  A work
+// Online softmax in the exp2 domain, fp32 state; the hardware's exp2 returns 0
+// below 2^-126, where a weight is nothing beside the row's largest (1); the
+// probabilities enter the P.V MFMA as a bf16 hi/lo pair, so they are not
+// rounded to bf16.  A work
 // item that covers all keys of its tokens writes the normalised output;
 // otherwise it writes (max, sum, unnormalised output) partials that
 // attn_combine merges in item order.  (Merging in the last-arriving wave
