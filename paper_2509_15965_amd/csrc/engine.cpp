@@ -1783,7 +1783,9 @@ rl_status rl_decode_create(const rl_model_config* cfg, const rl_weights* w, void
     };
     if (hipGetDevice(&c->device) != hipSuccess) return cleanup(RL_ERR_HIP);
     for (int i = 0; i < kStages; ++i) {
-        if (hipHostMalloc(reinterpret_cast<void**>(&c->staging[i]), align_up(L.meta_bytes, 16), hipHostMallocDefault) != hipSuccess ||
+        // coherent: a kernel reads what the host has just written, and caches none of it
+        if (hipHostMalloc(reinterpret_cast<void**>(&c->staging[i]), align_up(L.meta_bytes, 16),
+                          hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
             hipHostGetDevicePointer(reinterpret_cast<void**>(&c->staging_dev[i]), c->staging[i], 0) != hipSuccess)
             return cleanup(RL_ERR_HIP);
         if (hipEventCreateWithFlags(&c->stage_ev[i], hipEventDisableTiming) != hipSuccess)
