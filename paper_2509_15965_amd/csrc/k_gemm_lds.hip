@@ -807,7 +807,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_dma128_kernel(
         // (max, sum-exp) of every row over the tile's columns.  32 rows at a
         // time go through LDS (the ring is free by then) so that two lanes
         // hold a row's 64 columns of this wave; the four waves of a row meet
-        // in LDS.  About 4% of a tile of K 3584, against 13% for storing the
+        // in LDS.  About 5% of a tile of K 3584, against 13% for storing the
         // tile's logits and 8% for reading them back.  A target's logit leaves
         // from here too, the number that entered its row's sum: the log-sum-exp
         // is then never below it, and no log-probability above 0.
