@@ -44,10 +44,10 @@ BF16_PEAK_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 # HBM traffic of the attention kernel per algorithmic byte, from two
 # rocprofv3 --pmc runs (FETCH_SIZE, then WRITE_SIZE) of this benchmark's
 # default command, each counter scaled by what it reads for the library's
-# plain copy kernel of known size (FETCH_SIZE x 2.0, WRITE_SIZE x 1.0).  None:
-# the counters have not been taken since the kernel's loads and work items
-# last changed (they read 1.0950 before that).
-ATTN_TRAFFIC_PER_ALG_BYTE = None
+# plain copy kernel of known size (FETCH_SIZE x 2.0, WRITE_SIZE x 1.0).  Set it
+# to None when the kernel's loads or work items change, until the counters are
+# taken again.
+ATTN_TRAFFIC_PER_ALG_BYTE = 1.096
 
 
 def parse():
@@ -965,7 +965,7 @@ def main():
     roof["frac_of_measured_peak"] = round(roof["achieved"] / (peaks["hbm_read_GBps"] if roof["bound"] == "hbm"
                                                               else peaks["mfma_bf16_TFLOPs"]), 4)
     d = stats[dom]
-    if dom == "attention" and ATTN_TRAFFIC_PER_ALG_BYTE is not None:
+    if dom == "attention" and args.workload == "qwen7b" and ATTN_TRAFFIC_PER_ALG_BYTE is not None:
         roof["traffic"] = round(ATTN_TRAFFIC_PER_ALG_BYTE * d["alg_bytes"] / max(1, d["launches"]))
     classes = {c: {"launches": stats[c]["launches"],
                    "avg_launch_ms": round(stats[c]["total_ms"] / max(1, stats[c]["launches"]), 5),
